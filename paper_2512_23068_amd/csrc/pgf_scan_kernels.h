@@ -42,6 +42,7 @@ namespace pgf {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kThreads = 256;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- helpers
 
@@ -75,6 +76,14 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
+// a + b as an addition of its own (a product in a or b is rounded first):
+// the segment sums of dDelta_k, which kernels of different orders share bit
+// for bit.
+__device__ __forceinline__ float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 constexpr float kLog2eHi = 1.44269502162933349609375f;  // log2(e) rounded to f32
 constexpr float kLog2eLo = 1.925963033500011079e-08f;   // log2(e) - kLog2eHi
 constexpr float kLn2 = 0.693147180559945309f;
@@ -87,6 +96,55 @@ __device__ __forceinline__ float exp_nonpos(float v) {
     const float lo = fmaf(v, kLog2eHi, -p) + v * kLog2eLo;
     const float e = __builtin_amdgcn_exp2f(p);
     return fmaf(e, lo * kLn2, e);
+}
+
+// Runs of transcendental instructions.  Measured on gfx950 with four waves
+// per SIMD: f32 multiplies and fmas issue from two waves at a time (2.3
+// cycles each, 4.2 from one), but a v_exp_f32 or v_rcp_f32 that goes out
+// between other waves' fmas costs the SIMD 20-27 cycles, against 8 in a run
+// of its own.  Raising the wave's priority around the run keeps other waves'
+// instructions out of it (7.6 cycles each), so the kernels form all
+// arguments of a step first and evaluate them together here.  (The
+// s_setprio at the end is also the wait state between the last of them and
+// its first use.)
+__device__ __forceinline__ void exp2_run(float (&v)[1]) {
+    asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]));
+}
+__device__ __forceinline__ void exp2_run(float (&v)[2]) {
+    asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]));
+}
+__device__ __forceinline__ void exp2_run(float (&v)[4]) {
+    asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\t"
+                 "v_exp_f32 %3, %3\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+__device__ __forceinline__ void exp2_run(float (&v)[16]) {
+    asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\t"
+                 "v_exp_f32 %3, %3\n\tv_exp_f32 %4, %4\n\tv_exp_f32 %5, %5\n\tv_exp_f32 %6, %6\n\t"
+                 "v_exp_f32 %7, %7\n\tv_exp_f32 %8, %8\n\tv_exp_f32 %9, %9\n\tv_exp_f32 %10, %10\n\t"
+                 "v_exp_f32 %11, %11\n\tv_exp_f32 %12, %12\n\tv_exp_f32 %13, %13\n\tv_exp_f32 %14, %14\n\t"
+                 "v_exp_f32 %15, %15\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                   "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]),
+                   "+v"(v[14]), "+v"(v[15]));
+}
+__device__ __forceinline__ void rcp_run(float (&v)[2]) {
+    asm volatile("s_setprio 3\n\tv_rcp_f32 %0, %0\n\tv_rcp_f32 %1, %1\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]));
+}
+__device__ __forceinline__ void rcp_run(float (&v)[4]) {
+    asm volatile("s_setprio 3\n\tv_rcp_f32 %0, %0\n\tv_rcp_f32 %1, %1\n\tv_rcp_f32 %2, %2\n\t"
+                 "v_rcp_f32 %3, %3\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+__device__ __forceinline__ void rcp_run(float (&v)[8]) {
+    asm volatile("s_setprio 3\n\tv_rcp_f32 %0, %0\n\tv_rcp_f32 %1, %1\n\tv_rcp_f32 %2, %2\n\t"
+                 "v_rcp_f32 %3, %3\n\tv_rcp_f32 %4, %4\n\tv_rcp_f32 %5, %5\n\tv_rcp_f32 %6, %6\n\t"
+                 "v_rcp_f32 %7, %7\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                   "+v"(v[7]));
 }
 
 // Step size and its sensitivity factor for one (t, d):
@@ -109,6 +167,41 @@ __device__ __forceinline__ void discretize(float xv, float w, float bd, float &d
     delta = fmaxf(z, 0.0f) + 2.0f * sv * poly;
     const float r = __builtin_amdgcn_rcpf(1.0f + e);
     sw = (z >= 0.0f ? r : e * r) * w;
+}
+
+// discretize() of a lane's NC channels of a step, with their exponentials and
+// reciprocals in one run each (the same operations per channel).
+template <int NC, class V>
+__device__ __forceinline__ void discretize_lane(V xv, V w, V bd, V &delta, V &sw) {
+    float z[NC], e[NC], lo[NC], r[2 * NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        z[j] = fmaf(xv[j], w[j], bd[j]);
+        const float v = -fabsf(z[j]);
+        e[j] = v * kLog2eHi;
+        lo[j] = fmaf(v, kLog2eHi, -e[j]) + v * kLog2eLo;
+    }
+    exp2_run(e);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        e[j] = fmaf(e[j], lo[j] * kLn2, e[j]);
+        r[j] = 2.0f + e[j];
+        r[NC + j] = 1.0f + e[j];
+    }
+    rcp_run(r);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        const float sv = e[j] * r[j];
+        const float q = sv * sv;
+        float poly = fmaf(q, 1.0f / 13.0f, 1.0f / 11.0f);
+        poly = fmaf(q, poly, 1.0f / 9.0f);
+        poly = fmaf(q, poly, 1.0f / 7.0f);
+        poly = fmaf(q, poly, 1.0f / 5.0f);
+        poly = fmaf(q, poly, 1.0f / 3.0f);
+        poly = fmaf(q, poly, 1.0f);
+        delta[j] = fmaxf(z[j], 0.0f) + 2.0f * sv * poly;
+        sw[j] = (z[j] >= 0.0f ? r[NC + j] : e[j] * r[NC + j]) * w[j];
+    }
 }
 
 // Also returns sig = sigmoid(z) = dDelta/db (the parameter flows of the step
@@ -250,7 +343,6 @@ __device__ __forceinline__ void silu_and_slope(float v, float &f, float &df) {
 // accumulator r.  Each wave owns 16 * kProjRT rows and every column; the
 // channel order of the sum is fixed (ascending blocks of 4), whatever the
 // block of rows, so outputs do not depend on how the sequence is tiled.
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // Loads 4 consecutive values of one f32 row (zero from n on); vec: rows
 // and the row start are 4-element aligned.
@@ -856,9 +948,8 @@ __global__ __launch_bounds__(kThreads) void k_lowdt(
 // entry state at init[b*ibs + g*igs + c*ics + n*D + d] and write y, dy; if
 // end_state is set (sequential evaluation) the exit state is stored there
 // with the same indexing (g = 0).
-// Occupancy: one direction, f32 rows and the Euler drive fit four waves
-// per SIMD; two directions are held to three (a few registers spill outside
-// the step loop), except the ZOH aggregate pass, which spills inside it.
+// It serves the tilings with fewer than 16 states per thread and one thread
+// per channel (N = 4, 8; k_scan_m has the rest).
 template <int NT, int NS, int K, bool OUT, typename InT, int VAR = 0>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(K == 1 && (VAR & kZoh) == 0 && std::is_same<InT, float>::value ? 4
@@ -1126,6 +1217,517 @@ void k_scan(
             agg_s[base * D + d] = sD;
 #pragma unroll
             for (int k = 0; k < K; ++k) agg_s[(base + 1 + k) * D + d] = sdD[k];
+        }
+    }
+}
+
+// ---------------------------------------------------------------- k_scan_m
+// The scan for N = 16, 32, 64 states with the rank-one updates of the state
+// on the matrix cores.  v_mfma_f32_16x16x1_4b_f32 adds, in four independent
+// blocks, a column of 16 values times a row of 16: with lane (q, c) = (l/16,
+// l%16) of a wave, D_b[4q + r][c] += a[lane 16b + 4q + r] * b[lane 16b + c]
+// in accumulator 4b + r.  Rows are states and columns are channels, so one
+// instruction is B_t[n] * u[d] for 16 states of 64 channels (1024 fmas in 32
+// cycles, exactly rounded fmas).  N = 16*M: block b covers states 16*(b/NC)
+// .. +15 of channel b % NC of each column, NC = 4/M; a lane holds NC
+// consecutive channels x 4M states and a wave CH = 16*NC channels.
+//   h'    = mfma(B, u, Abar*h)
+//   dh_k' = mfma(dB_k, u, mfma(B, p_k, Abar*dh_k + (A Abar h) dDelta_k))
+// The elementwise products, the exponentials and the sums over states stay
+// on the vector unit.
+//
+// What bounds it: vector issue together with the clock, which the card lowers
+// under this load (about 1.85 GHz measured, against 2.15 in a form with the
+// same products as vector fmas reading the records from scalar registers).
+// At pulse128k sizes (B = 1, L = 131072, D = 1536, N = 16, f32, normal dx)
+// that form took 1.10 ms (aggregate) and 1.33 ms (outputs) with one
+// direction, 1.51 and 1.85 with two, 1.98 and 1.99 with the ZOH drive; this
+// one 0.91 and 1.22, 1.24 and 1.83, 1.63 and 1.86.  Leaving out the matrix
+// updates, the exponentials, the discretisation or the loads and stores
+// saves 0.22, 0.10, 0.11 and 0.18 ms of the 1.22: no one of them dominates.
+// One direction runs four waves per SIMD (126 VGPRs, 37 KB of LDS a block);
+// two directions and the ZOH drive two.
+//
+// Everything a wave shares goes through its own LDS slice (no block barrier;
+// a wave's LDS operations complete in order), a tile of four steps at a time:
+//   - lane (q, c) loads step q of the tile for its channels (one vector load
+//     per sequence), forms their step sizes and leaves the per-channel
+//     scalars of that step in the step's slot;
+//   - the tile's step records are copied to LDS as they lie;
+//   - each step reads its scalars and its share of the record; the partial
+//     outputs over the lane's states go back to the step's slot (its scalars
+//     have been read by then), and at the end of the tile lane (q, c) sums
+//     the four partials of step q for its channels and stores them.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+template <int NC>
+struct LaneVec;   // NC consecutive channels
+template <>
+struct LaneVec<4> {
+    typedef float F __attribute__((ext_vector_type(4)));
+    typedef float FU __attribute__((ext_vector_type(4), aligned(4)));
+    typedef unsigned int HU __attribute__((ext_vector_type(2), aligned(2)));
+};
+template <>
+struct LaneVec<2> {
+    typedef float F __attribute__((ext_vector_type(2)));
+    typedef float FU __attribute__((ext_vector_type(2), aligned(4)));
+    typedef unsigned int HU __attribute__((ext_vector_type(1), aligned(2)));
+};
+template <>
+struct LaneVec<1> {
+    typedef float F __attribute__((ext_vector_type(1)));
+    typedef float FU __attribute__((ext_vector_type(1)));
+};
+template <int NC>
+using lanevec = typename LaneVec<NC>::F;
+
+// NC consecutive elements from a uniform base at a 32-bit element offset
+// (element alignment); the row has nd elements from there, or at least NC.
+template <int NC>
+__device__ __forceinline__ lanevec<NC> load_lane(const float *__restrict__ base, uint32_t i, int nd) {
+    const float *p = (const float *)((const char *)base + (size_t)(i * 4u));
+    if (NC == 1 || nd >= NC) return *(const typename LaneVec<NC>::FU *)p;
+    lanevec<NC> v;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) v[j] = p[j < nd ? j : nd - 1];
+    return v;
+}
+template <int NC>
+__device__ __forceinline__ lanevec<NC> load_lane(const uint16_t *__restrict__ base, uint32_t i, int nd) {
+    const uint16_t *p = (const uint16_t *)((const char *)base + (size_t)(i * 2u));
+    lanevec<NC> v;
+    if constexpr (NC > 1) {
+        if (nd >= NC) {
+            const typename LaneVec<NC>::HU u = *(const typename LaneVec<NC>::HU *)p;
+#pragma unroll
+            for (int j = 0; j < NC / 2; ++j) {
+                v[2 * j] = __uint_as_float(u[j] << 16);
+                v[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
+            }
+            return v;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) v[j] = __uint_as_float(((uint32_t)p[j < nd ? j : nd - 1]) << 16);
+    return v;
+}
+template <int NC>
+__device__ __forceinline__ void store_lane(float *__restrict__ base, uint32_t i, int nd, lanevec<NC> v) {
+    float *p = (float *)((char *)base + (size_t)(i * 4u));
+    if (NC == 1 || nd >= NC) {
+        *(typename LaneVec<NC>::FU *)p = v;
+    } else {
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+            if (j < nd) p[j] = v[j];
+    }
+}
+
+// Orders a wave's LDS accesses across its lanes (they execute in program
+// order; this only keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int M, int K, bool OUT, typename InT, int VAR = 0>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(K == 1 && (VAR & kZoh) == 0 ? 4 : 2)))
+void k_scan_m(
+    const InT *__restrict__ x, const InT *__restrict__ dx, const float *__restrict__ A,
+    const float *__restrict__ w_delta, const float *__restrict__ b_delta, const float *__restrict__ bc,
+    const float *__restrict__ init, int64_t ibs, int64_t igs, int64_t ics,
+    float *__restrict__ y, float *__restrict__ dy, float *__restrict__ end_state,
+    float *__restrict__ agg_h, float *__restrict__ agg_s,
+    int64_t Bsz, int64_t L, int64_t D, int64_t t0, int64_t len, int64_t Tc, int64_t S, int G, Variant vr) {
+    constexpr int N = 16 * M;
+    constexpr int NC = 4 / M;                // channels per lane
+    constexpr int R = 2 * N * (1 + K);
+    constexpr bool LR = (VAR & kLowRank) != 0;
+    constexpr bool ZOH = (VAR & kZoh) != 0;
+    constexpr int CH = 16 * NC;              // channels per wave
+    constexpr int TT = 4;                    // steps per tile
+    constexpr int F = 2 + 2 * K;             // scalars per channel and step
+    constexpr int O = 1 + K;
+    constexpr int SLOT = OUT && O * 4 > F ? O * 4 * CH : F * CH;   // floats of a step's slot
+    constexpr int RU = TT * R / 4;           // float4s of a tile's records
+    constexpr int RV = (RU + 63) / 64;
+    constexpr int KZ = LR ? 1 + K : 0;
+    typedef lanevec<NC> LV;
+    __shared__ __align__(16) float s_step[4][TT * SLOT];
+    __shared__ floatx4 s_rec[4][RU];
+    __shared__ __align__(16) float s_wb[4][2 * CH];   // w_delta, b_delta of the wave's channels
+
+    const int lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int c = lane % 16, q = lane / 16;
+    const int Di = (int)D;
+    const int d0 = ((int)blockIdx.x * 4 + wave) * CH;
+    const int g = blockIdx.y;
+    const int64_t b = blockIdx.z;
+    const int ts = (int)(g * S);             // steps of a host block fit 30 bits
+    const int te = (int)(ts + S < len ? ts + S : len);
+    if (d0 >= Di || ts >= te) return;
+    // A lane past the last channels computes the last NC again (the same
+    // bits, stored twice).
+    const int cb = Di < NC ? 0 : (d0 + NC * c < Di - NC ? d0 + NC * c : Di - NC);
+    float *step = s_step[wave];
+    floatx4 *recs = s_rec[wave];
+    float *wb = s_wb[wave] + NC * c;
+
+    // Element e = 4 blk + r of a lane's state is state 16 (blk/NC) + 4q + r of
+    // channel cb + blk % NC.
+    float Af[16], Ai[16], Dr[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        const int64_t dj = cb + j < Di ? cb + j : Di - 1;
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const floatx4 av = *(const typename LaneVec<4>::FU *)(A + dj * N + 16 * m + 4 * q);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                Af[4 * (m * NC + j) + r] = av[r];
+                if constexpr (ZOH) Ai[4 * (m * NC + j) + r] = 1.0f / av[r];
+            }
+        }
+        if constexpr (!LR) {
+            wb[j] = w_delta[dj];
+            wb[CH + j] = b_delta[dj];
+        }
+        Dr[j] = 0.0f;
+        if constexpr ((VAR & kOutMap) != 0 && OUT) Dr[j] = vr.D_res ? vr.D_res[dj] : 0.0f;
+    }
+
+    floatx16 h, dh[K];
+    if constexpr (OUT) {
+        const float *ib = init + b * ibs + g * igs;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t o = (uint32_t)((16 * m + 4 * q + r) * Di + cb);
+                const LV v = load_lane<NC>(ib, o, Di);
+#pragma unroll
+                for (int j = 0; j < NC; ++j) h[4 * (m * NC + j) + r] = v[j];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const LV dv = load_lane<NC>(ib + (1 + k) * ics, o, Di);
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) dh[k][4 * (m * NC + j) + r] = dv[j];
+                }
+            }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            h[e] = 0.0f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) dh[k][e] = 0.0f;
+        }
+    }
+    LV sD, sdD[K];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        sD[j] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) sdD[k][j] = 0.0f;
+    }
+
+    const int64_t dxs = Bsz * L * D;  // stride between directions
+    const InT *Xb = x + (b * L + t0) * D;
+    const InT *DXb = dx + (b * L + t0) * D;
+    float *Yb = y + (b * L + t0) * D;
+    float *DYb = dy + (b * L + t0) * D;
+    // Records of the wave's channel group (a group is a multiple of 64
+    // channels, so a wave lies in one); with groups a step holds G records.
+    int Rt = R;
+    const float *rec0 = bc + b * Tc * R;
+    if constexpr ((VAR & kGroups) != 0) {
+        Rt = vr.groups * R;
+        rec0 = bc + b * Tc * Rt + (d0 / (int)vr.group_ch) * R;
+    }
+    const float *Zb = nullptr;
+    if constexpr (LR) Zb = vr.z + b * Tc * D;
+
+    LV xn, dxn[K], zn[1 + K];
+    floatx4 rn[RV];
+    auto fetch = [&](int tb) {
+        const uint32_t o = (uint32_t)(tb + q < te ? tb + q : te - 1) * (uint32_t)Di + (uint32_t)cb;
+        xn = load_lane<NC>(Xb, o, Di);
+#pragma unroll
+        for (int k = 0; k < K; ++k) dxn[k] = load_lane<NC>(DXb + k * dxs, o, Di);
+#pragma unroll
+        for (int k = 0; k < KZ; ++k) zn[k] = load_lane<NC>(Zb + k * vr.zs, o, Di);
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            int e = lane + 64 * i;
+            if (RU % 64 != 0) e = e < RU ? e : RU - 1;
+            const int tr = tb + e / (R / 4);
+            rn[i] = *(const floatx4 *)(rec0 + (int64_t)(tr < te ? tr : te - 1) * Rt + 4 * (e % (R / 4)));
+        }
+    };
+    fetch(ts);
+
+    for (int tb = ts; tb < te; tb += TT) {
+        // --- this lane's step (tb + q) of its channels
+        const LV xv = xn;
+        LV dxv[K], delta, dD[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) dxv[k] = dxn[k];
+        if constexpr (LR) {
+            delta = zn[0];
+#pragma unroll
+            for (int k = 0; k < K; ++k) dD[k] = zn[1 + k];
+        } else {
+            LV sw;
+            discretize_lane<NC>(xv, *(const LV *)wb, *(const LV *)(wb + CH), delta, sw);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int j = 0; j < NC; ++j) dD[k][j] = sw[j] * dxv[k][j];
+        }
+        if (tb + TT > te) {
+            // a step past the segment leaves the state exactly as it is
+            // (Abar = 1, no drive); its outputs are not stored
+            const bool live = tb + q < te;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                delta[j] = live ? delta[j] : 0.0f;
+#pragma unroll
+                for (int k = 0; k < K; ++k) dD[k][j] = live ? dD[k][j] : 0.0f;
+            }
+        }
+        {
+            // scalars of the step, one row of CH channels each: Euler
+            // Delta log2(e), u, dDelta_k, p_k; ZOH Delta, x, dDelta_k, dx_k
+            float *sc = step + q * SLOT + NC * c;
+            LV f0, f1, f3[K];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                f0[j] = ZOH ? delta[j] : delta[j] * kLog2e;
+                f1[j] = ZOH ? xv[j] : delta[j] * xv[j];
+                if constexpr (!OUT) sD[j] += delta[j];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    f3[k][j] = ZOH ? dxv[k][j] : fmaf(dD[k][j], xv[j], delta[j] * dxv[k][j]);
+                    if constexpr (!OUT) sdD[k][j] = add_rounded(sdD[k][j], dD[k][j]);
+                }
+            }
+            *(LV *)sc = f0;
+            *(LV *)(sc + CH) = f1;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                *(LV *)(sc + (2 + 2 * k) * CH) = dD[k];
+                *(LV *)(sc + (3 + 2 * k) * CH) = f3[k];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RV; ++i)
+            if (RU % 64 == 0 || lane + 64 * i < RU) recs[lane + 64 * i] = rn[i];
+        fetch(tb + TT);
+        wave_lds_fence();
+
+        // --- the steps; each reads the next one's scalars and mfma operands
+        // ahead of its own arithmetic
+        LV n0, n2[K];
+        float n1, n3[K], nB, ndB[K];
+        auto read_step = [&](int t) {
+            const float *sc = step + t * SLOT + NC * c;
+            const float *ra = (const float *)recs + t * R + 16 * (q / NC) + c;   // this lane's rows of the mfma
+            n0 = *(const LV *)sc;
+            n1 = sc[CH + q % NC];                               // its column: channel cb + q % NC
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                n2[k] = *(const LV *)(sc + (2 + 2 * k) * CH);
+                n3[k] = sc[(3 + 2 * k) * CH + q % NC];
+            }
+            nB = ra[0];
+#pragma unroll
+            for (int k = 0; k < K; ++k) ndB[k] = ra[(1 + k) * N];
+        };
+        read_step(0);
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+            const float *rec = (const float *)recs + t * R;
+            const LV f0 = n0;
+            LV f2[K];
+            const float f1 = n1, Ba = nB;
+            float f3[K], dBa[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                f2[k] = n2[k];
+                f3[k] = n3[k];
+                dBa[k] = ndB[k];
+            }
+            if (t + 1 < TT) read_step(t + 1);
+            floatx16 a;
+            {
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int j = (e / 4) % NC;
+                    v[e] = fmaf(ZOH ? f0[j] * kLog2e : f0[j], Af[e], kExp2Lift);
+                }
+                exp2_run(v);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) a[e] = v[e];
+            }
+            if constexpr (ZOH) {
+                // b = e B x, db_k = Abar dDelta_k B x + e (dB_k x + B dx_k);
+                // with the transition's term A Abar h dDelta_k the dDelta_k
+                // terms share the factor Abar B x + g.
+                floatx16 zero;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) zero[e] = 0.0f;
+                const floatx16 Bx = __builtin_amdgcn_mfma_f32_16x16x1f32(Ba, f1, zero, 0, 0, 0);
+                floatx16 J[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    J[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(Ba, f3[k], zero, 0, 0, 0);
+                    J[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(dBa[k], f1, J[k], 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int j = (e / 4) % NC;
+                    const float sv = a[e] * h[e];
+                    const float gv = Af[e] * sv;
+                    const float ec = zoh_coef(f0[j], Af[e], Ai[e], a[e]);
+                    const float r = fmaf(a[e], Bx[e], gv);
+                    h[e] = fmaf(ec, Bx[e], sv);
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+                        dh[k][e] = fmaf(a[e], dh[k][e], fmaf(f2[k][j], r, ec * J[k][e]));
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int j = (e / 4) % NC;
+                    h[e] *= a[e];
+                    const float gv = Af[e] * h[e];
+#pragma unroll
+                    for (int k = 0; k < K; ++k) dh[k][e] = fmaf(gv, f2[k][j], a[e] * dh[k][e]);
+                }
+                h = __builtin_amdgcn_mfma_f32_16x16x1f32(Ba, f1, h, 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    dh[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(Ba, f3[k], dh[k], 0, 0, 0);
+                    dh[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(dBa[k], f1, dh[k], 0, 0, 0);
+                }
+            }
+            if constexpr (OUT) {
+                LV yv, dyv[K];
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const floatx4 Cv = *(const floatx4 *)(rec + (1 + K) * N + 16 * m + 4 * q);
+                    floatx4 dCv[K];
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+                        dCv[k] = *(const floatx4 *)(rec + (2 + K + k) * N + 16 * m + 4 * q);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int j = 0; j < NC; ++j) {
+                            const int e = 4 * (m * NC + j) + r;
+                            const bool first = m == 0 && r == 0;
+                            yv[j] = first ? Cv[r] * h[e] : fmaf(Cv[r], h[e], yv[j]);
+#pragma unroll
+                            for (int k = 0; k < K; ++k) {
+                                dyv[k][j] = first ? dCv[k][r] * h[e] : fmaf(dCv[k][r], h[e], dyv[k][j]);
+                                dyv[k][j] = fmaf(Cv[r], dh[k][e], dyv[k][j]);
+                            }
+                        }
+                }
+                wave_lds_fence();   // the slot's scalars have been read
+                float *po = step + t * SLOT + q * CH + NC * c;
+                *(LV *)po = yv;
+#pragma unroll
+                for (int k = 0; k < K; ++k) *(LV *)(po + (1 + k) * 4 * CH) = dyv[k];
+            }
+        }
+
+        // --- outputs of this lane's step
+        if constexpr (OUT) {
+            wave_lds_fence();
+            const float *po = step + q * SLOT + NC * c;
+            LV ov[O];
+#pragma unroll
+            for (int o = 0; o < O; ++o) {
+                ov[o] = *(const LV *)(po + o * 4 * CH);
+#pragma unroll
+                for (int s2 = 1; s2 < 4; ++s2) {
+                    const LV pv = *(const LV *)(po + (o * 4 + s2) * CH);
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) ov[o][j] += pv[j];
+                }
+            }
+            if constexpr ((VAR & kOutMap) != 0) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                    ov[0][j] = fmaf(Dr[j], xv[j], ov[0][j]);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) ov[1 + k][j] = fmaf(Dr[j], dxv[k][j], ov[1 + k][j]);
+                }
+                if (vr.act == PGF_ACT_SILU) {
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) {
+                        float f, df;
+                        silu_and_slope(ov[0][j], f, df);
+                        ov[0][j] = f;
+#pragma unroll
+                        for (int k = 0; k < K; ++k) ov[1 + k][j] *= df;
+                    }
+                }
+            }
+            if (tb + q < te) {
+                const uint32_t o = (uint32_t)(tb + q) * (uint32_t)Di + (uint32_t)cb;
+                store_lane<NC>(Yb, o, Di, ov[0]);
+#pragma unroll
+                for (int k = 0; k < K; ++k) store_lane<NC>(DYb + k * dxs, o, Di, ov[1 + k]);
+            }
+        }
+        wave_lds_fence();   // the next tile overwrites the slots
+    }
+
+    auto put_state = [&](float *dst, int64_t plane) {
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t o = (uint32_t)((16 * m + 4 * q + r) * Di + cb);
+                LV v;
+#pragma unroll
+                for (int j = 0; j < NC; ++j) v[j] = h[4 * (m * NC + j) + r];
+                store_lane<NC>(dst, o, Di, v);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) v[j] = dh[k][4 * (m * NC + j) + r];
+                    store_lane<NC>(dst + (1 + k) * plane, o, Di, v);
+                }
+            }
+    };
+    if constexpr (OUT) {
+        if (end_state) put_state(end_state + b * ibs, ics);
+    } else {
+        const int64_t base = (b * G + g) * (1 + K);
+        put_state(agg_h + base * N * D, N * D);
+        // the sums of Delta and dDelta_k: each lane holds those of its own
+        // steps (q modulo 4), added here in the order of q
+        *(LV *)(step + q * CH + NC * c) = sD;
+#pragma unroll
+        for (int k = 0; k < K; ++k) *(LV *)(step + ((1 + k) * 4 + q) * CH + NC * c) = sdD[k];
+        wave_lds_fence();
+#pragma unroll
+        for (int o = 0; o < O; ++o) {
+            if (q != o) continue;
+            LV v = *(const LV *)(step + o * 4 * CH + NC * c);
+#pragma unroll
+            for (int s2 = 1; s2 < 4; ++s2) {
+                const LV pv = *(const LV *)(step + (o * 4 + s2) * CH + NC * c);
+#pragma unroll
+                for (int j = 0; j < NC; ++j) v[j] += pv[j];
+            }
+            store_lane<NC>(agg_s + (base + o) * D, (uint32_t)cb, Di, v);
         }
     }
 }
@@ -1445,12 +2047,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
     }
 }
 
-// Kernel for a tiling: one thread per channel, or several sharing one.
+// Kernel for a tiling: 16 states per thread (K <= 2, N = 16, 32, 64) run on
+// the matrix cores; with fewer, one thread per channel or several sharing one.
 // The aggregate pass (OUT = false) writes no outputs, so it drops the
 // output map of a variant.
 template <int NT, int NS, int K, bool OUT, typename InT, int VAR>
 constexpr auto scan_kernel() {
-    if constexpr (NS == 1) return &k_scan<NT, NS, K, OUT, InT, OUT ? VAR : (VAR & (kZoh | kGroups | kLowRank))>;
+    constexpr int V = OUT ? VAR : (VAR & (kZoh | kGroups | kLowRank));
+    if constexpr (NT == 16) return &k_scan_m<NS, K, OUT, InT, V>;
+    else if constexpr (NS == 1) return &k_scan<NT, NS, K, OUT, InT, V>;
     else return &k_scan_sh<NT, NS, K, OUT, InT>;
 }
 
@@ -1491,11 +2096,15 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
     const int64_t te = ts + S < len ? ts + S : len;
     if (ts >= te) return;
 
-    float Af[NT], At[NT];
+    // With 16 states per thread the operations of h, hv, hw and of their
+    // outputs follow k_scan_m (matrix-core updates last, partial sums over
+    // four states), with fewer k_scan, so that y and dy equal theirs.
+    constexpr bool MORD = NT == 16;
+    float Af[NT], At[MORD ? 1 : NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         Af[i] = A[d * N + ns * NT + i];
-        At[i] = Af[i] * kLog2e;
+        if constexpr (!MORD) At[i] = Af[i] * kLog2e;
     }
     const float w = w_delta[d], bd = b_delta[d];
 
@@ -1513,7 +2122,11 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
 #pragma unroll
         for (int i = 0; i < NT; ++i) h[i] = hv[i] = hw[i] = hvw[i] = 0.0f;
     }
-    float sD = 0.0f, sDv = 0.0f, sDw = 0.0f, sDvw = 0.0f;
+    // sums over the segment; with MORD one per step modulo 4, as k_scan_m's
+    constexpr int NSUM = MORD ? 4 : 1;
+    float sD[NSUM], sDv[NSUM], sDw[NSUM], sDvw = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NSUM; ++j) sD[j] = sDv[j] = sDw[j] = 0.0f;
 
     const int64_t dxs = Bsz * L * D;
     const InT *Xb = x + (b * L + t0) * D;
@@ -1569,17 +2182,27 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
                 const float q = fmaf(dvw, xv, fmaf(dv, wv, dw * vv));
                 const float c1 = dv * dw;
                 if constexpr (!OUT) {
-                    sD += delta;
-                    sDv += dv;
-                    sDw += dw;
+                    sD[j % NSUM] += delta;
+                    sDv[j % NSUM] = add_rounded(sDv[j % NSUM], dv);
+                    sDw[j % NSUM] = add_rounded(sDw[j % NSUM], dw);
                     sDvw += dvw;
                 }
                 const float *rec = rec0 + t * R + ns * NT;
                 float yv = 0.0f, y1 = 0.0f, y2 = 0.0f, y3 = 0.0f;
+                float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f;   // partial outputs of four states (MORD)
+                float av[MORD ? NT : 1];
+                if constexpr (MORD) {
+                    const float dl = delta * kLog2e;
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) av[i] = fmaf(dl, Af[i], kExp2Lift);
+                    exp2_run(av);
+                }
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     const float Bn = rec[i], dBv = rec[N + i], dBw = rec[2 * N + i];
-                    const float a = transition(delta, At[i]);
+                    float a;
+                    if constexpr (MORD) a = av[i];
+                    else a = transition(delta, At[i]);
                     const float sv = a * h[i];
                     const float gv = Af[i] * sv;
                     const float hn = fmaf(Bn, u, sv);
@@ -1587,17 +2210,34 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
                     const float cvw = fmaf(Af[i], c1, dvw);
                     const float cross = fmaf(dw, hv[i], fmaf(dv, hw[i], cvw * h[i]));
                     const float hvwn = fmaf(a, hvw[i], fmaf(Af[i] * a, cross, fmaf(Bn, q, fmaf(dBv, pw, dBw * pv))));
-                    const float hvn = fmaf(a, hv[i], fmaf(gv, dv, fmaf(Bn, pv, dBv * u)));
-                    const float hwn = fmaf(a, hw[i], fmaf(gv, dw, fmaf(Bn, pw, dBw * u)));
+                    float hvn, hwn;
+                    if constexpr (MORD) {
+                        hvn = fmaf(dBv, u, fmaf(Bn, pv, fmaf(gv, dv, a * hv[i])));
+                        hwn = fmaf(dBw, u, fmaf(Bn, pw, fmaf(gv, dw, a * hw[i])));
+                    } else {
+                        hvn = fmaf(a, hv[i], fmaf(gv, dv, fmaf(Bn, pv, dBv * u)));
+                        hwn = fmaf(a, hw[i], fmaf(gv, dw, fmaf(Bn, pw, dBw * u)));
+                    }
                     h[i] = hn;
                     hv[i] = hvn;
                     hw[i] = hwn;
                     hvw[i] = hvwn;
                     if constexpr (OUT) {
                         const float Cn = rec[3 * N + i], dCv = rec[4 * N + i], dCw = rec[5 * N + i];
-                        yv = fmaf(Cn, hn, yv);
-                        y1 = fmaf(dCv, hn, fmaf(Cn, hvn, y1));
-                        y2 = fmaf(dCw, hn, fmaf(Cn, hwn, y2));
+                        if constexpr (MORD) {
+                            p0 = i % 4 == 0 ? Cn * hn : fmaf(Cn, hn, p0);
+                            p1 = fmaf(Cn, hvn, i % 4 == 0 ? dCv * hn : fmaf(dCv, hn, p1));
+                            p2 = fmaf(Cn, hwn, i % 4 == 0 ? dCw * hn : fmaf(dCw, hn, p2));
+                            if (i % 4 == 3) {
+                                yv = i == 3 ? p0 : yv + p0;
+                                y1 = i == 3 ? p1 : y1 + p1;
+                                y2 = i == 3 ? p2 : y2 + p2;
+                            }
+                        } else {
+                            yv = fmaf(Cn, hn, yv);
+                            y1 = fmaf(dCv, hn, fmaf(Cn, hvn, y1));
+                            y2 = fmaf(dCw, hn, fmaf(Cn, hwn, y2));
+                        }
                         y3 = fmaf(Cn, hvwn, fmaf(dCw, hvn, fmaf(dCv, hwn, y3)));
                     }
                 }
@@ -1654,9 +2294,15 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
             agg_h[((base + 3) * N + n) * D + d] = hvw[i];
         }
         if (ns != 0) return;   // the per-channel sums once
-        agg_s[base * D + d] = sD;
-        agg_s[(base + 1) * D + d] = sDv;
-        agg_s[(base + 2) * D + d] = sDw;
+#pragma unroll
+        for (int j = 1; j < NSUM; ++j) {
+            sD[0] += sD[j];
+            sDv[0] += sDv[j];
+            sDw[0] += sDw[j];
+        }
+        agg_s[base * D + d] = sD[0];
+        agg_s[(base + 1) * D + d] = sDv[0];
+        agg_s[(base + 2) * D + d] = sDw[0];
         agg_s[(base + 3) * D + d] = sDvw;
     }
 }
@@ -1833,10 +2479,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
     constexpr int R = 2 * N;          // B, C
     constexpr int CP = DLT ? 5 : 3;   // state planes per lane
     constexpr int NW = DLT ? NT : 1;
-    // With both the ZOH drive and the step size's flows the exponent scale
-    // A log2(e) is formed per step (the same product, so the same bits)
-    // instead of held, to stay within the registers.
-    constexpr bool ATF = ZOH && DLT;
+    // With 16 states per thread the operations of h and y follow k_scan_m
+    // (Delta scaled by log2(e), partial sums over four states), with fewer
+    // k_scan, so that y equals theirs.  There, with both the ZOH drive and the
+    // step size's flows, the exponent scale A log2(e) is formed per step (the
+    // same product, so the same bits) instead of held, to stay within the
+    // registers.
+    constexpr bool MORD = NT == 16;
+    constexpr bool ATF = MORD || (ZOH && DLT);
     // prefetch depth, bounded by the VGPR budget
     constexpr int TT = OUT && NT >= 16 ? (MAP || DLT ? 2 : 4) : 8;
 
@@ -1855,7 +2505,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         if constexpr (!ATF) At[i] = A[d * N + ns * NT + i] * kLog2e;
-        if constexpr (ZOH || DLT) Af[i] = A[d * N + ns * NT + i];
+        if constexpr (ATF || ZOH || DLT) Af[i] = A[d * N + ns * NT + i];
         if constexpr (ZOH) Ai[i] = 1.0f / Af[i];
     }
     const float w = w_delta[d], bd = b_delta[d];
@@ -1883,7 +2533,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
 #pragma unroll
         for (int i = 0; i < NW; ++i) gw[i] = gs[i] = 0.0f;
     }
-    float sD = 0.0f;
+    // with MORD the sum of Delta is kept per step modulo 4, as k_scan_m's
+    constexpr int NSUM = MORD ? 4 : 1;
+    float sD[NSUM];
+#pragma unroll
+    for (int j = 0; j < NSUM; ++j) sD[j] = 0.0f;
     float sSx = 0.0f, sS = 0.0f;   // aggregate pass, DLT: sums of sigma x and sigma
     float sW = 0.0f, sG = 0.0f;    // output pass, DLT: the per-channel accumulations
 
@@ -1926,7 +2580,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
                 const float u = delta * xv;
                 const float sgx = sig * xv;
                 if constexpr (!OUT) {
-                    sD += delta;
+                    sD[j % NSUM] += delta;
                     if constexpr (DLT) {
                         sSx += sgx;
                         sS += sig;
@@ -1934,13 +2588,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
                 }
                 const float *rec = rec0 + t * R + ns * NT;   // this thread's lanes
                 float yv = 0.0f, cw = 0.0f, cs = 0.0f;
+                float p0 = 0.0f;   // partial output of four states (MORD)
+                float av[MORD ? NT : 1];
+                if constexpr (MORD) {
+                    const float dl = delta * kLog2e;
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) av[i] = fmaf(dl, Af[i], kExp2Lift);
+                    exp2_run(av);
+                }
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     const float Bn = rec[i];
-                    float at;
-                    if constexpr (ATF) at = Af[i] * kLog2e;
-                    else at = At[i];
-                    const float a = transition(delta, at);
+                    float a;
+                    if constexpr (MORD) a = av[i];
+                    else if constexpr (ATF) a = transition(delta, Af[i] * kLog2e);
+                    else a = transition(delta, At[i]);
                     const float sv = a * h[i];
                     if constexpr (ZOH) {
                         const float e = zoh_coef(delta, Af[i], Ai[i], a);
@@ -1966,7 +2628,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
                     }
                     if constexpr (OUT) {
                         const float Cn = rec[N + i];
-                        yv = fmaf(Cn, h[i], yv);
+                        if constexpr (MORD) {
+                            p0 = i % 4 == 0 ? Cn * h[i] : fmaf(Cn, h[i], p0);
+                            if (i % 4 == 3) yv = i == 3 ? p0 : yv + p0;
+                        } else {
+                            yv = fmaf(Cn, h[i], yv);
+                        }
                         if constexpr (DLT) {
                             cw = fmaf(Cn, gw[i], cw);
                             cs = fmaf(Cn, gs[i], cs);
@@ -2078,7 +2745,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
             }
         }
         if (ns != 0) return;   // the per-channel sums once
-        agg_s[base * D + d] = sD;
+#pragma unroll
+        for (int j = 1; j < NSUM; ++j) sD[0] += sD[j];
+        agg_s[base * D + d] = sD[0];
         if constexpr (DLT) {
             agg_s[(base + 1) * D + d] = sSx;
             agg_s[(base + 2) * D + d] = sS;

@@ -1,0 +1,68 @@
+"""The scan with 16 states per thread (k_scan_m) at the edges of its tiles:
+fewer channels than a lane holds, channel counts around a wave's and a
+block's, sequences around its four-step tiles and the segment length, rows
+that are not 16-byte aligned, both input types and several states per
+channel.  Against the fp64 oracle (relative L2 1e-5 per output, the gate of
+every f32 path), with guard values around the outputs."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_23068_amd import binding
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 64
+SENTINEL = 1.25e30
+
+
+def _guarded(shape):
+    n = int(np.prod(shape))
+    buf = torch.full((n + 2 * GUARD,), SENTINEL, device=gu.dev())
+    return buf, buf[GUARD:GUARD + n].view(shape)
+
+
+def _case(N, K, D, L, B=1, bf16=False, seg=0, **kw):
+    what = f"N={N} K={K} D={D} L={L} B={B} bf16={bf16} seg={seg} {kw}"
+    print(f"case {what}", flush=True)
+    inp = gu.custom("stiff128k" if bf16 else "mamba130m", batch=B, seqlen=L, d_inner=D, d_state=N, n_dirs=K)
+    if kw.get("dres"):
+        inp["D_res"] = np.random.default_rng(2).standard_normal(D).astype(np.float32)
+    opts = {k: kw[k] for k in ("drive", "act") if k in kw}
+    x, dx = gu.inputs_to_dev(inp)
+    ybuf, y = _guarded((B, L, D))
+    dbuf, dy = _guarded((K, B, L, D))
+    binding.scan_jvp(x, dx, gu.params_to_dev(inp), out=(y, dy), seg_len=seg, **opts)
+    torch.cuda.synchronize()
+    yo, dyo, _, _ = oracle.scan_jvp(inp["x"], inp["dx"], inp, **opts)
+    gu.assert_close(y.cpu().numpy(), dy.cpu().numpy(), yo, dyo, what=what)
+    for buf in (ybuf, dbuf):
+        assert torch.all(buf[:GUARD] == SENTINEL) and torch.all(buf[-GUARD:] == SENTINEL), what
+
+
+@pytest.mark.parametrize("D", [1, 2, 3, 4, 5, 7, 63, 65, 130, 255, 257])
+def test_channel_edges(D):
+    _case(16, 1, D, 21)
+    _case(16, 2, D, 9, bf16=True)
+
+
+@pytest.mark.parametrize("N,D", [(32, 1), (32, 31), (32, 33), (32, 130), (64, 1), (64, 15), (64, 17), (64, 66)])
+def test_wide_states(N, D):
+    _case(N, 1, D, 22)
+    _case(N, 2, D, 18, bf16=True)
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 8, 15, 16, 17, 31, 32, 33, 67])
+def test_step_edges(L):
+    """Segments of 16 steps: lengths around the tile and the segment."""
+    _case(16, 1, 70, L, B=2, seg=16)
+    _case(32, 1, 37, L, seg=-1)
+
+
+@pytest.mark.parametrize("drive,act,dres", [("zoh", "identity", False), ("zoh", "silu", True), ("euler", "silu", True),
+                                            ("euler", "identity", True)])
+@pytest.mark.parametrize("K", [1, 2])
+def test_variants_at_odd_sizes(drive, act, dres, K):
+    _case(16, K, 67, 37, B=2, seg=16, drive=drive, act=act, dres=dres)
