@@ -9,7 +9,7 @@
 //            (dx_k W) -- the contraction over channels, Sec. 3 selective maps.
 //   k_scan<false>  segment aggregate: each segment scanned from a zero state;
 //            writes its end state (h0, dh0_k) and the sums of Delta, dDelta_k.
-//   k_carry  sequential over the block's segments, per lane: composes the
+//   k_carry_t  sequential over the block's segments, per lane: composes the
 //            segment operators (Prop. 3.2, Eq. 5 summed over a segment:
 //            P = exp(A sum Delta), Q_k = P A sum dDelta_k) into the true
 //            state entering each segment.  Division-free: P underflowing to
@@ -359,6 +359,8 @@ __device__ __forceinline__ floatx4 load4(const float *__restrict__ row, int64_t 
 // acc[rt][c] receives the 16x16 tile (rows wave*32 + rt*16 .., columns
 // c*16 ..) of src[r0.., 0..dn) * W, where wload(d, j) is W[d][j] (d counted
 // from src) for j < NC (zero is returned past the matrix).
+// Up to 32 columns the sums of rst stages of 32 channels are formed
+// separately and added in order.
 // X tiles are staged through LDS with the next channel stage in flight; the
 // channel order of the sum is fixed.  Three forms (xw_tiles picks one):
 // f32 rows on v_mfma_f32_16x16x4f32 (xw_tiles_f32); bf16 rows on
@@ -369,6 +371,25 @@ constexpr int kProjRT = 2;                      // 16-row tiles per wave
 constexpr int kProjTM = 4 * 16 * kProjRT;       // rows per block
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Channels per range of the sums over channels (k_proj with up to 32
+// columns): the sum of each range is formed first and the ranges are added in
+// order, in one block or, where a launch has few rows, with a block per range
+// (k_psum); both give the same bits.
+constexpr int kProjRange = 256;
+
+// tot = first range's tiles, then tot += the next one's; acc starts anew.
+template <int CT>
+__device__ __forceinline__ void add_tiles(floatx4 (&tot)[kProjRT][CT], floatx4 (&acc)[kProjRT][CT], bool more) {
+#pragma unroll
+    for (int rt = 0; rt < kProjRT; ++rt)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tot[rt][c][r] = more ? tot[rt][c][r] + acc[rt][c][r] : acc[rt][c][r];
+            acc[rt][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+}
 
 // bf16 rows: the products x*W run exactly on the bf16 matrix cores.  W (f32)
 // is cut into three bf16 planes, hi = W with its significand truncated to 8
@@ -382,7 +403,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // every fragment is one 16-byte LDS read.
 template <int NC, class WLoad>
 __device__ __forceinline__ void xw_tiles_bf16(const uint16_t *__restrict__ src, int64_t ld, int64_t dn, int64_t len,
-                                              int64_t r0, WLoad wload, floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
+                                              int64_t r0, WLoad wload, int64_t rst, floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
     constexpr int CT = (NC + 15) / 16;
     constexpr int NCP = CT * 16;
     constexpr int RT = kProjRT;
@@ -459,35 +480,57 @@ __device__ __forceinline__ void xw_tiles_bf16(const uint16_t *__restrict__ src, 
         for (int c = 0; c < CT; ++c) acc[rt][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int64_t nst = (dn + DT - 1) / DT;
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int64_t st = 0; st < nst; ++st) {
-        const int buf = (int)(st & 1);
-        if (st + 1 < nst) fetch((st + 1) * DT);
-        bf16x8 a[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-            a[rt] = *(const bf16x8 *)&Xs[buf][wave * 16 * RT + rt * 16 + lane % 16][8 * (lane / 16)];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            bf16x8 bv[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) bv[q] = *(const bf16x8 *)&Ws[buf][q][c * 16 + lane % 16][8 * (lane / 16)];
+    floatx4 tot[RT][CT];     // the ranges before the current one
+    bool more = false;
+    // (the ranges start the pipeline anew: 1 % of the time at 1536 channels,
+    // where carrying it across them kept the sums out of the accumulators and
+    // cost 13 %)
+    const int64_t range = NC <= 32 ? rst : nst;
+    for (int64_t s0 = 0; s0 < nst; s0 += range) {
+        const int64_t se = s0 + range < nst ? s0 + range : nst;
+        if (s0 > 0) {
+            add_tiles<CT>(tot, acc, more);
+            more = true;
+        }
+        fetch(s0 * DT);
+        stash(0);
+        __syncthreads();
+        int buf = 0;
+#pragma unroll 1
+        for (int64_t st = s0; st < se; ++st) {
+            if (st + 1 < se) fetch((st + 1) * DT);
+            bf16x8 a[RT];
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
+                a[rt] = *(const bf16x8 *)&Xs[buf][wave * 16 * RT + rt * 16 + lane % 16][8 * (lane / 16)];
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt], bv[q], acc[rt][c], 0, 0, 0);
+            for (int c = 0; c < CT; ++c) {
+                bf16x8 bv[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) bv[q] = *(const bf16x8 *)&Ws[buf][q][c * 16 + lane % 16][8 * (lane / 16)];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt], bv[q], acc[rt][c], 0, 0, 0);
+            }
+            if (st + 1 < se) stash(buf ^ 1);
+            __syncthreads();
+            buf ^= 1;
         }
-        if (st + 1 < nst) stash(buf ^ 1);
-        __syncthreads();
+    }
+    if (NC <= 32 && more) {
+        add_tiles<CT>(tot, acc, true);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[rt][c] = tot[rt][c];
     }
 }
 
 template <int NC, class WLoad>
 __device__ __forceinline__ void xw_tiles_f32(const float *__restrict__ src, int64_t ld, int64_t dn, int64_t len,
-                                             int64_t r0, WLoad wload, floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
+                                             int64_t r0, WLoad wload, int64_t rst, floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
     constexpr int CT = (NC + 15) / 16;  // 16-column tiles (zero-padded)
     constexpr int NCP = CT * 16;
     constexpr int RT = kProjRT;
@@ -542,27 +585,49 @@ __device__ __forceinline__ void xw_tiles_f32(const float *__restrict__ src, int6
         for (int c = 0; c < CT; ++c) acc[rt][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int64_t nst = (dn + DT - 1) / DT;
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int64_t st = 0; st < nst; ++st) {
-        const int buf = (int)(st & 1);
-        if (st + 1 < nst) fetch((st + 1) * DT);
-#pragma unroll
-        for (int kk = 0; kk < DT / 4; ++kk) {
-            float bv[CT];
-#pragma unroll
-            for (int c = 0; c < CT; ++c) bv[c] = Ws[buf][kk * 4 + lane / 16][c * 16 + lane % 16];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const float a = Xs[buf][wave * 16 * RT + rt * 16 + lane % 16][kk * 4 + lane / 16];
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-                    acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[c], acc[rt][c], 0, 0, 0);
-            }
+    floatx4 tot[RT][CT];     // the ranges before the current one
+    bool more = false;
+    // (the ranges start the pipeline anew: 1 % of the time at 1536 channels,
+    // where carrying it across them kept the sums out of the accumulators and
+    // cost 13 %)
+    const int64_t range = NC <= 32 ? rst : nst;
+    for (int64_t s0 = 0; s0 < nst; s0 += range) {
+        const int64_t se = s0 + range < nst ? s0 + range : nst;
+        if (s0 > 0) {
+            add_tiles<CT>(tot, acc, more);
+            more = true;
         }
-        if (st + 1 < nst) stash(buf ^ 1);
+        fetch(s0 * DT);
+        stash(0);
         __syncthreads();
+        int buf = 0;
+#pragma unroll 1
+        for (int64_t st = s0; st < se; ++st) {
+            if (st + 1 < se) fetch((st + 1) * DT);
+#pragma unroll
+            for (int kk = 0; kk < DT / 4; ++kk) {
+                float bv[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) bv[c] = Ws[buf][kk * 4 + lane / 16][c * 16 + lane % 16];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const float a = Xs[buf][wave * 16 * RT + rt * 16 + lane % 16][kk * 4 + lane / 16];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[c], acc[rt][c], 0, 0, 0);
+                }
+            }
+            if (st + 1 < se) stash(buf ^ 1);
+            __syncthreads();
+            buf ^= 1;
+        }
+    }
+    if (NC <= 32 && more) {
+        add_tiles<CT>(tot, acc, true);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[rt][c] = tot[rt][c];
     }
 }
 
@@ -705,10 +770,11 @@ __device__ __forceinline__ void xw_tiles_split(const float *__restrict__ src, in
 
 template <int NC, typename InT, class WLoad>
 __device__ __forceinline__ void xw_tiles(const InT *__restrict__ src, int64_t ld, int64_t dn, int64_t len,
-                                         int64_t r0, WLoad wload, floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
-    if constexpr (std::is_same<InT, uint16_t>::value) xw_tiles_bf16<NC>(src, ld, dn, len, r0, wload, acc);
+                                         int64_t r0, WLoad wload, int64_t rst,
+                                         floatx4 (&acc)[kProjRT][(NC + 15) / 16]) {
+    if constexpr (std::is_same<InT, uint16_t>::value) xw_tiles_bf16<NC>(src, ld, dn, len, r0, wload, rst, acc);
     else if constexpr (NC >= 64) xw_tiles_split<NC>(src, ld, dn, len, r0, wload, acc);
-    else xw_tiles_f32<NC>(src, ld, dn, len, r0, wload, acc);
+    else xw_tiles_f32<NC>(src, ld, dn, len, r0, wload, rst, acc);
 }
 
 // Row source s = blockIdx.y: 0 -> x, 1+k -> dx_k, of batch b = blockIdx.z.
@@ -721,9 +787,10 @@ __device__ __forceinline__ const InT *row_source(const InT *x, const InT *dx, in
 // Per-step projections of one host block.  Grid (ceil(len/128) * S, 1+KP,
 // B): rows of x (s = 0) or dx_{s-1} times [W_B | W_C] (NC = 2 * groups * N
 // columns) give B, dB_k, C, dC_k (per group), with the biases on s = 0.
-// With S > 1 splits the channel sum is cut into S ranges of dchunk
-// channels: split 0 writes bc (with the biases), split q > 0 writes the
-// same records to part + (q-1) * part_stride, and k_psum adds them in order.
+// With S > 1 splits the channel sum is cut into S parts of dchunk channels:
+// split 0 writes bc, split q > 0 the same records, len of them per batch row,
+// to part + (q-1) * part_stride, and k_psum adds them in order, then the
+// biases.  Within a split the sums of rst 32-channel stages are added in order.
 // The grouped 128-column form is held to 256 VGPRs (two waves per SIMD): it
 // took 260 and ran one block per CU, which left each stage's global loads
 // exposed.  (The hint reschedules the other forms, which measured faster
@@ -733,7 +800,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NC >= 
     const InT *__restrict__ x, const InT *__restrict__ dx, const float *__restrict__ WB,
     const float *__restrict__ WC, const float *__restrict__ bB, const float *__restrict__ bC,
     float *__restrict__ bc, int64_t Bsz, int64_t L, int64_t D, int K, int64_t t0, int64_t len, int64_t Tc,
-    int gn, int S, int64_t dchunk, float *__restrict__ part, int64_t part_stride) {
+    int gn, int S, int64_t dchunk, int64_t rst, float *__restrict__ part, int64_t part_stride) {
     constexpr int N = NC / 2;
     constexpr int CT = (NC + 15) / 16;
     constexpr int RT = kProjRT;
@@ -746,16 +813,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NC >= 
     const int64_t dn = D - dlo < dchunk ? D - dlo : dchunk;
     if (q > 0) {
         bc = part + (int64_t)(q - 1) * part_stride;
-        bB = nullptr;
-        bC = nullptr;
+        Tc = len;
     }
+    if (S > 1) bB = bC = nullptr;
     floatx4 acc[RT][CT];
     xw_tiles<NC, InT>(row_source(x, dx, s, b, Bsz, L, t0, D) + dlo, D, dn, len, r0,
                       [&](int64_t d, int j) {
                           const int64_t dd = dlo + d;
                           return j < N ? WB[dd * N + j] : WC[dd * N + (j - N)];
                       },
-                      acc);
+                      rst, acc);
     const int R = 2 * N * (1 + K);     // a step's records (all groups)
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -784,15 +851,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NC >= 
     }
 }
 
-// bc[i] += part[0][i] + ... in split order, for the n floats of a host
-// block's records (S > 1 channel splits).
+// Adds the S parts of a host block's records (grid y = batch row, len*R
+// floats each): the parts of each per consecutive ones first, then those
+// sums, in order, then the biases of B and C on the rows of x (records of
+// 2 gn (1+K) floats per group, [B | dB_k | C | dC_k]).
 static __global__ __launch_bounds__(kThreads) void k_psum(float *__restrict__ bc, const float *__restrict__ part,
-                                                         int64_t part_stride, int S, int64_t n) {
+                                                         int64_t part_stride, int S, int per, int64_t len, int64_t Tc,
+                                                         int R, int gn, int K, const float *__restrict__ bB,
+                                                         const float *__restrict__ bC) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    float v = bc[i];
-    for (int q = 1; q < S; ++q) v += part[(int64_t)(q - 1) * part_stride + i];
-    bc[i] = v;
+    const int64_t b = blockIdx.y;
+    if (i >= len * R) return;
+    float *out = bc + b * Tc * R + i;
+    const float *pb = part + b * len * R + i;
+    float tot = 0.0f, v = *out;
+    for (int q = 1; q < S; ++q) {
+        const float w = pb[(int64_t)(q - 1) * part_stride];
+        if (q % per == 0) {
+            tot = q == per ? v : tot + v;
+            v = w;
+        } else {
+            v += w;
+        }
+    }
+    if (S > per) v = tot + v;
+    const int pos = (int)(i % R), rec = 2 * gn * (1 + K), g = pos / rec, in = pos % rec;
+    if (bB && in < gn) v += bB[g * gn + in];
+    if (bC && in >= gn * (1 + K) && in < gn * (2 + K)) v += bC[g * gn + in - gn * (1 + K)];
+    *out = v;
 }
 
 // ---------------------------------------------------------------- low-rank step size
@@ -828,7 +914,7 @@ __global__ __launch_bounds__(kThreads) void k_lowx(
     const int64_t r0 = (int64_t)blockIdx.x * kProjTM;
     floatx4 acc[RT][CT];
     xw_tiles<RC, InT>(row_source(x, dx, s, b, Bsz, L, t0, D), D, D, len, r0,
-                      [&](int64_t d, int j) { return j < R ? Wdx[d * R + j] : 0.0f; }, acc);
+                      [&](int64_t d, int j) { return j < R ? Wdx[d * R + j] : 0.0f; }, (D + 31) / 32, acc);
     float *out = lr + ((int64_t)s * Bsz + b) * Tc * RC;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -1354,10 +1440,15 @@ void k_scan_m(
     constexpr int RU = TT * R / 4;           // float4s of a tile's records
     constexpr int RV = (RU + 63) / 64;
     constexpr int KZ = LR ? 1 + K : 0;
+    constexpr bool MAP = (VAR & kOutMap) != 0 && OUT;
+    // Reading a step's operands one step ahead takes 12 registers; with the
+    // output map, the low-rank planes or several states per channel they
+    // would spill at four waves per SIMD, and the reads stay with their step.
+    constexpr bool AHEAD = !(K == 1 && !ZOH && (MAP || LR || M > 1));
     typedef lanevec<NC> LV;
     __shared__ __align__(16) float s_step[4][TT * SLOT];
     __shared__ floatx4 s_rec[4][RU];
-    __shared__ __align__(16) float s_wb[4][2 * CH];   // w_delta, b_delta of the wave's channels
+    __shared__ __align__(16) float s_wb[4][3 * CH];   // w_delta, b_delta, D_res of the wave's channels
 
     const int lane = threadIdx.x % 64;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
@@ -1378,7 +1469,7 @@ void k_scan_m(
 
     // Element e = 4 blk + r of a lane's state is state 16 (blk/NC) + 4q + r of
     // channel cb + blk % NC.
-    float Af[16], Ai[16], Dr[NC];
+    float Af[16], Ai[16];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
         const int64_t dj = cb + j < Di ? cb + j : Di - 1;
@@ -1395,8 +1486,7 @@ void k_scan_m(
             wb[j] = w_delta[dj];
             wb[CH + j] = b_delta[dj];
         }
-        Dr[j] = 0.0f;
-        if constexpr ((VAR & kOutMap) != 0 && OUT) Dr[j] = vr.D_res ? vr.D_res[dj] : 0.0f;
+        if constexpr (MAP) wb[2 * CH + j] = vr.D_res ? vr.D_res[dj] : 0.0f;
     }
 
     floatx16 h, dh[K];
@@ -1528,7 +1618,7 @@ void k_scan_m(
         wave_lds_fence();
 
         // --- the steps; each reads the next one's scalars and mfma operands
-        // ahead of its own arithmetic
+        // ahead of its own arithmetic (AHEAD)
         LV n0, n2[K];
         float n1, n3[K], nB, ndB[K];
         auto read_step = [&](int t) {
@@ -1545,9 +1635,10 @@ void k_scan_m(
 #pragma unroll
             for (int k = 0; k < K; ++k) ndB[k] = ra[(1 + k) * N];
         };
-        read_step(0);
+        if constexpr (AHEAD) read_step(0);
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
+            if constexpr (!AHEAD) read_step(t);
             const float *rec = (const float *)recs + t * R;
             const LV f0 = n0;
             LV f2[K];
@@ -1559,7 +1650,7 @@ void k_scan_m(
                 f3[k] = n3[k];
                 dBa[k] = ndB[k];
             }
-            if (t + 1 < TT) read_step(t + 1);
+            if (AHEAD && t + 1 < TT) read_step(t + 1);
             floatx16 a;
             {
                 float v[16];
@@ -1660,7 +1751,8 @@ void k_scan_m(
                     for (int j = 0; j < NC; ++j) ov[o][j] += pv[j];
                 }
             }
-            if constexpr ((VAR & kOutMap) != 0) {
+            if constexpr (MAP) {
+                const LV Dr = *(const LV *)(wb + 2 * CH);
 #pragma unroll
                 for (int j = 0; j < NC; ++j) {
                     ov[0][j] = fmaf(Dr[j], xv[j], ov[0][j]);
@@ -2307,124 +2399,172 @@ __attribute__((amdgpu_waves_per_eu(NS > 1 ? 2 : (OUT || !std::is_same<InT, float
     }
 }
 
-// Carry of the second-order flow: each segment acts on (h, hv, hw, hvw) as
+// ---------------------------------------------------------------- carries
+// The state entering each segment of a host block: per lane (b, n, d) the
+// segments' maps are composed one after the other (state [comp][B][N][D]
+// enters the block and leaves it; seg [B][G][CP][N][D] holds each segment's
+// end state from a zero start on entry and is overwritten with the true
+// state entering it).  Only the chain itself is sequential (a few dependent
+// fmas per segment): a block owns 64 lanes and its waves take consecutive
+// runs of GB segments each, load them and form their transition coefficients
+// at the same time, and then pass the state from wave to wave through LDS.
+// Bound by memory for many lanes: 24 576 lanes (D = 1536, N = 16, one
+// direction) and 512 segments, 0.2 GB, take 49 us (4.1 TB/s), 128 segments of
+// the parameter flows 29 us, of the complex transition 29 us; one thread per
+// lane walking all segments took 109, 52 and 66 us.
+// A policy P gives CP state planes, CS sums per segment (of the SS planes of
+// agg_s), NP transition coefficients, GB, and the map itself.
+constexpr int kCarryWaves = 8;
+
+// Block barrier that orders LDS only: a __syncthreads here would also wait
+// for every global store in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Grid (ceil(N*D/64), B).  Four waves per SIMD: two blocks per CU, so that the
+// lanes of one batch row of 1536 channels are resident at once.
+template <class P>
+__global__ __launch_bounds__(64 * kCarryWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_carry_t(
+    const float *__restrict__ A, const float *__restrict__ Aim, float *seg, const float *__restrict__ agg_s,
+    float *__restrict__ state, int64_t Bsz, int64_t D, int64_t N, int G) {
+    constexpr int CP = P::CP, CS = P::CS, SS = P::SS, NP = P::NP, GB = P::GB;
+    __shared__ float s_st[CP][64];
+    const int l = threadIdx.x % 64;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int W = (int)blockDim.x / 64;
+    const int64_t ND = N * D;
+    const uint32_t raw = blockIdx.x * 64 + l;
+    const bool live = raw < (uint32_t)ND;
+    const uint32_t r = live ? raw : (uint32_t)ND - 1;   // lanes past the end repeat the last one and store nothing
+    const uint32_t n = r / (uint32_t)D, d = r - n * (uint32_t)D;
+    const int64_t b = blockIdx.y;
+    const int64_t cs = Bsz * ND;
+    const P pol(A[(int64_t)d * N + n], Aim ? Aim[(int64_t)d * N + n] : 0.0f);
+    float *sb = state + b * ND;
+    if (w == 0) {
+#pragma unroll
+        for (int c = 0; c < CP; ++c) s_st[c][l] = load_in(sb + c * cs, r);
+    }
+    lds_barrier();
+    for (int t0 = 0; t0 < G; t0 += W * GB) {
+        const int g0 = t0 + w * GB;
+        const int ng = G - g0 < GB ? G - g0 : GB;      // segments of this wave (may be <= 0)
+        float *sg = seg + ((b * G + g0) * CP) * ND;
+        const float *sm = agg_s + ((b * G + g0) * SS) * D;
+        float e[GB][CP], co[GB][NP];
+#pragma unroll
+        for (int j = 0; j < GB; ++j) {
+            if (j < ng) {
+#pragma unroll
+                for (int c = 0; c < CP; ++c) e[j][c] = load_in(sg + (j * CP + c) * ND, r);
+#pragma unroll
+                for (int c = 0; c < CS; ++c) co[j][c] = load_in(sm + (j * SS + c) * D, d);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < GB; ++j) pol.coef(co[j]);
+        for (int w0 = 0; w0 < W && t0 + w0 * GB < G; ++w0) {
+            if (w == w0) {
+                float st[CP];
+#pragma unroll
+                for (int c = 0; c < CP; ++c) st[c] = s_st[c][l];
+#pragma unroll
+                for (int j = 0; j < GB; ++j) {
+                    if (j < ng) {
+                        if (live) {
+#pragma unroll
+                            for (int c = 0; c < CP; ++c) store_out(sg + (j * CP + c) * ND, r, st[c]);
+                        }
+                        pol.step(st, e[j], co[j]);
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < CP; ++c) s_st[c][l] = st[c];
+            }
+            lds_barrier();
+        }
+    }
+    if (w == 0 && live) {
+#pragma unroll
+        for (int c = 0; c < CP; ++c) store_out(sb + c * cs, r, s_st[c][l]);
+    }
+}
+
+// First order: h' = P h + h0, dh_k' = P dh_k + Q_k h + dh0_k, P = exp(A sum
+// Delta), Q_k = P A sum dDelta_k.
+template <int K>
+struct CarryFirst {
+    static constexpr int CP = 1 + K, CS = 1 + K, SS = 1 + K, NP = 1 + K, GB = K <= 1 ? 8 : (K <= 4 ? 4 : 2);
+    const float a, at;
+    __device__ __forceinline__ CarryFirst(float a_, float) : a(a_), at(a_ * kLog2e) {}
+    __device__ __forceinline__ void coef(float (&c)[NP]) const {
+        c[0] = exp2_series(at * c[0]);
+#pragma unroll
+        for (int k = 0; k < K; ++k) c[1 + k] = c[0] * (a * c[1 + k]);
+    }
+    __device__ __forceinline__ void step(float (&st)[CP], const float (&e)[CP], const float (&c)[NP]) const {
+#pragma unroll
+        for (int k = 0; k < K; ++k) st[1 + k] = fmaf(c[0], st[1 + k], fmaf(c[1 + k], st[0], e[1 + k]));
+        st[0] = fmaf(c[0], st[0], e[0]);
+    }
+};
+
+// Second-order flow: each segment acts on (h, hv, hw, hvw) as
 //   h' = P h + h0, hv' = P hv + Pv h + hv0, hw' = P hw + Pw h + hw0,
 //   hvw' = P hvw + Pw hv + Pv hw + Pvw h + hvw0,
 // P = 2^(At S), Pv = P (A Sv), Pw = P (A Sw), Pvw = P ((A Sv)(A Sw) + A Svw):
 // the derivatives of the segment's map h_in -> P h_in + h0 along v, w.
-static __global__ __launch_bounds__(kThreads) void k_carry2(
-    const float *__restrict__ A, float *__restrict__ seg, const float *__restrict__ agg_s,
-    float *__restrict__ state, int64_t Bsz, int64_t D, int64_t N, int G) {
-    constexpr int GB = 16;
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t ND = N * D;
-    if (idx >= Bsz * ND) return;
-    const int64_t d = idx % D, n = (idx / D) % N, b = idx / ND;
-    const float a = A[d * N + n];
-    const float at = a * kLog2e;
-    const int64_t cs = Bsz * ND;
-    const int64_t lane = n * D + d;
-    float h = state[b * ND + lane], hv = state[cs + b * ND + lane];
-    float hw = state[2 * cs + b * ND + lane], hvw = state[3 * cs + b * ND + lane];
-    for (int g0 = 0; g0 < G; g0 += GB) {
-        float e0[GB], e1[GB], e2[GB], e3[GB], s0[GB], s1[GB], s2[GB], s3[GB];
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            const int g = g0 + j < G ? g0 + j : G - 1;
-            const int64_t base = (b * G + g) * 4;
-            e0[j] = seg[base * ND + lane];
-            e1[j] = seg[(base + 1) * ND + lane];
-            e2[j] = seg[(base + 2) * ND + lane];
-            e3[j] = seg[(base + 3) * ND + lane];
-            s0[j] = agg_s[base * D + d];
-            s1[j] = agg_s[(base + 1) * D + d];
-            s2[j] = agg_s[(base + 2) * D + d];
-            s3[j] = agg_s[(base + 3) * D + d];
-        }
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            if (g0 + j >= G) break;
-            const int64_t base = (b * G + g0 + j) * 4;
-            seg[base * ND + lane] = h;
-            seg[(base + 1) * ND + lane] = hv;
-            seg[(base + 2) * ND + lane] = hw;
-            seg[(base + 3) * ND + lane] = hvw;
-            const float P = exp2_series(at * s0[j]);
-            const float asv = a * s1[j], asw = a * s2[j];
-            const float Pv = P * asv, Pw = P * asw;
-            const float Pvw = P * fmaf(asv, asw, a * s3[j]);
-            const float hvw1 = fmaf(P, hvw, fmaf(Pw, hv, fmaf(Pv, hw, fmaf(Pvw, h, e3[j]))));
-            const float hv1 = fmaf(P, hv, fmaf(Pv, h, e1[j]));
-            const float hw1 = fmaf(P, hw, fmaf(Pw, h, e2[j]));
-            h = fmaf(P, h, e0[j]);
-            hv = hv1;
-            hw = hw1;
-            hvw = hvw1;
-        }
+struct CarrySecond {
+    static constexpr int CP = 4, CS = 4, SS = 4, NP = 4, GB = 4;
+    const float a, at;
+    __device__ __forceinline__ CarrySecond(float a_, float) : a(a_), at(a_ * kLog2e) {}
+    __device__ __forceinline__ void coef(float (&c)[NP]) const {
+        const float P = exp2_series(at * c[0]);
+        const float asv = a * c[1], asw = a * c[2];
+        c[0] = P;
+        c[1] = P * asv;
+        c[2] = P * asw;
+        c[3] = P * fmaf(asv, asw, a * c[3]);
     }
-    state[b * ND + lane] = h;
-    state[cs + b * ND + lane] = hv;
-    state[2 * cs + b * ND + lane] = hw;
-    state[3 * cs + b * ND + lane] = hvw;
-}
+    __device__ __forceinline__ void step(float (&st)[CP], const float (&e)[CP], const float (&c)[NP]) const {
+        st[3] = fmaf(c[0], st[3], fmaf(c[2], st[1], fmaf(c[1], st[2], fmaf(c[3], st[0], e[3]))));
+        st[1] = fmaf(c[0], st[1], fmaf(c[1], st[0], e[1]));
+        st[2] = fmaf(c[0], st[2], fmaf(c[2], st[0], e[2]));
+        st[0] = fmaf(c[0], st[0], e[0]);
+    }
+};
 
-// ---------------------------------------------------------------- k_carry
-// One thread per lane (b, n, d), sequential over the block's segments.
-// state [(1+K)][B][N][D] enters the block and leaves it.  seg [B][G][(1+K)]
-// [N][D] holds each segment's end state from a zero start on entry and is
-// overwritten, segment by segment, with the true state entering it.  Loads
-// for GB segments are issued together so their latencies overlap.
-template <int K>
-__global__ __launch_bounds__(kThreads) void k_carry(
-    const float *__restrict__ A, float *__restrict__ seg, const float *__restrict__ agg_s,
-    float *__restrict__ state, int64_t Bsz, int64_t D, int64_t N, int G) {
-    constexpr int GB = K == 1 ? 32 : (K == 2 ? 16 : (K == 4 ? 8 : 4));
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t ND = N * D;
-    if (idx >= Bsz * ND) return;
-    const int64_t d = idx % D, n = (idx / D) % N, b = idx / ND;
-    const float a = A[d * N + n];
-    const float at = a * kLog2e;
-    const int64_t cstride = Bsz * ND;  // state: component stride
-    const int64_t lane = n * D + d;
-    float h = state[b * ND + lane];
-    float dh[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) dh[k] = state[(1 + k) * cstride + b * ND + lane];
-    for (int g0 = 0; g0 < G; g0 += GB) {
-        float h0[GB], dh0[GB][K], sD[GB], sdD[GB][K];
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            const int g = g0 + j < G ? g0 + j : G - 1;
-            const int64_t base = (b * G + g) * (1 + K);
-            h0[j] = seg[base * ND + lane];
-            sD[j] = agg_s[base * D + d];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                dh0[j][k] = seg[(base + 1 + k) * ND + lane];
-                sdD[j][k] = agg_s[(base + 1 + k) * D + d];
-            }
+// Parameter flows: a segment maps its entry state to
+//   h' = P h + h0,  GA' = P GA + S P h + GA0,  GB' = P GB + GB0,
+// P = exp(A S), S = the segment's sum of Delta (dP/dA = S P).  DLT: the
+// step size's flows go the same way with dP/dtheta = P A S_theta, S_theta
+// the segment's sum of dDelta/dtheta (sigma x for w_delta, sigma for
+// b_delta; agg_s components 1 and 2):
+//   Gw' = P Gw + P A S_w h + Gw0,  Gs' = P Gs + P A S_s h + Gs0.
+template <bool DLT>
+struct CarryParam {
+    static constexpr int CP = DLT ? 5 : 3, CS = DLT ? 3 : 1, SS = CP, NP = DLT ? 4 : 2, GB = 4;
+    const float a, at;
+    __device__ __forceinline__ CarryParam(float a_, float) : a(a_), at(a_ * kLog2e) {}
+    __device__ __forceinline__ void coef(float (&c)[NP]) const {
+        const float s0 = c[0], P = exp2_series(at * s0);
+        if constexpr (DLT) {
+            const float PA = P * a;
+            c[3] = PA * c[2];
+            c[2] = PA * c[1];
         }
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            if (g0 + j >= G) break;
-            const int64_t base = (b * G + g0 + j) * (1 + K);
-            seg[base * ND + lane] = h;
-#pragma unroll
-            for (int k = 0; k < K; ++k) seg[(base + 1 + k) * ND + lane] = dh[k];
-            const float P = exp2_series(at * sD[j]);
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const float q = P * (a * sdD[j][k]);
-                dh[k] = fmaf(P, dh[k], fmaf(q, h, dh0[j][k]));
-            }
-            h = fmaf(P, h, h0[j]);
-        }
+        c[0] = P;
+        c[1] = P * s0;
     }
-    state[b * ND + lane] = h;
-#pragma unroll
-    for (int k = 0; k < K; ++k) state[(1 + k) * cstride + b * ND + lane] = dh[k];
-}
+    __device__ __forceinline__ void step(float (&st)[CP], const float (&e)[CP], const float (&c)[NP]) const {
+        if constexpr (DLT) {
+            st[3] = fmaf(c[0], st[3], fmaf(c[2], st[0], e[3]));
+            st[4] = fmaf(c[0], st[4], fmaf(c[3], st[0], e[4]));
+        }
+        st[1] = fmaf(c[0], st[1], fmaf(c[1], st[0], e[1]));
+        st[2] = fmaf(c[0], st[2], e[2]);
+        st[0] = fmaf(c[0], st[0], e[0]);
+    }
+};
 
 // ---------------------------------------------------------------- parameter flows
 // Sensitivity flows of the parameters with online gradient accumulation
@@ -2752,82 +2892,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ZOH ||
             agg_s[(base + 1) * D + d] = sSx;
             agg_s[(base + 2) * D + d] = sS;
         }
-    }
-}
-
-// Carry of the parameter flows: a segment maps its entry state to
-//   h' = P h + h0,  GA' = P GA + S P h + GA0,  GB' = P GB + GB0,
-// P = exp(A S), S = the segment's sum of Delta (dP/dA = S P).  DLT: the
-// step size's flows go the same way with dP/dtheta = P A S_theta, S_theta
-// the segment's sum of dDelta/dtheta (sigma x for w_delta, sigma for
-// b_delta; agg_s components 1 and 2):
-//   Gw' = P Gw + P A S_w h + Gw0,  Gs' = P Gs + P A S_s h + Gs0.
-// Same layout (CP planes per segment) and in-place convention as k_carry.
-template <bool DLT>
-__global__ __launch_bounds__(kThreads) void k_pcarry(
-    const float *__restrict__ A, float *__restrict__ seg, const float *__restrict__ agg_s,
-    float *__restrict__ state, int64_t Bsz, int64_t D, int64_t N, int G) {
-    constexpr int GB = 16;
-    constexpr int CP = DLT ? 5 : 3;
-    constexpr int NX = DLT ? GB : 1;
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t ND = N * D;
-    if (idx >= Bsz * ND) return;
-    const int64_t d = idx % D, n = (idx / D) % N, b = idx / ND;
-    const float a = A[d * N + n];
-    const float at = a * kLog2e;
-    const int64_t cs = Bsz * ND;
-    const int64_t lane = n * D + d;
-    float h = state[b * ND + lane], ga = state[cs + b * ND + lane], gb = state[2 * cs + b * ND + lane];
-    float gw = 0.0f, gs = 0.0f;
-    if constexpr (DLT) {
-        gw = state[3 * cs + b * ND + lane];
-        gs = state[4 * cs + b * ND + lane];
-    }
-    for (int g0 = 0; g0 < G; g0 += GB) {
-        float e0[GB], e1[GB], e2[GB], s0[GB];
-        float e3[NX], e4[NX], s1[NX], s2[NX];
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            const int g = g0 + j < G ? g0 + j : G - 1;
-            const int64_t base = (b * G + g) * CP;
-            e0[j] = seg[base * ND + lane];
-            e1[j] = seg[(base + 1) * ND + lane];
-            e2[j] = seg[(base + 2) * ND + lane];
-            s0[j] = agg_s[base * D + d];
-            if constexpr (DLT) {
-                e3[j] = seg[(base + 3) * ND + lane];
-                e4[j] = seg[(base + 4) * ND + lane];
-                s1[j] = agg_s[(base + 1) * D + d];
-                s2[j] = agg_s[(base + 2) * D + d];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            if (g0 + j >= G) break;
-            const int64_t base = (b * G + g0 + j) * CP;
-            seg[base * ND + lane] = h;
-            seg[(base + 1) * ND + lane] = ga;
-            seg[(base + 2) * ND + lane] = gb;
-            const float P = exp2_series(at * s0[j]);
-            if constexpr (DLT) {
-                seg[(base + 3) * ND + lane] = gw;
-                seg[(base + 4) * ND + lane] = gs;
-                const float PA = P * a;
-                gw = fmaf(P, gw, fmaf(PA * s1[j], h, e3[j]));
-                gs = fmaf(P, gs, fmaf(PA * s2[j], h, e4[j]));
-            }
-            ga = fmaf(P, ga, fmaf(P * s0[j], h, e1[j]));
-            gb = fmaf(P, gb, e2[j]);
-            h = fmaf(P, h, e0[j]);
-        }
-    }
-    state[b * ND + lane] = h;
-    state[cs + b * ND + lane] = ga;
-    state[2 * cs + b * ND + lane] = gb;
-    if constexpr (DLT) {
-        state[3 * cs + b * ND + lane] = gw;
-        state[4 * cs + b * ND + lane] = gs;
     }
 }
 
@@ -3229,63 +3293,42 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
     }
 }
 
-// Carry of the complex scan: a segment maps (h, dh_k) to (P h + h0,
-// P dh_k + Q_k h + dh0_k) with P = exp(A S) (complex), Q_k = P A S_k, S and
-// S_k the segment sums of Delta and dDelta_k.  Layout as k_carry with the
-// state split into planes (seg [B][G][2(1+K)][N][D], agg_s [B][G][1+K][D]).
+// Carry of the complex transition: the first order's map with complex P =
+// exp(A sum Delta) and Q_k = P A sum dDelta_k, planes (re, im) of h, dh_k.
 template <int K>
-__global__ __launch_bounds__(kThreads) void k_ccarry(
-    const float *__restrict__ A, const float *__restrict__ Aim, float *__restrict__ seg,
-    const float *__restrict__ agg_s, float *__restrict__ state, int64_t Bsz, int64_t D, int64_t N, int G) {
-    constexpr int GB = 8;
-    constexpr int CP = 2 * (1 + K);
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t ND = N * D;
-    if (idx >= Bsz * ND) return;
-    const int64_t d = idx % D, n = (idx / D) % N, b = idx / ND;
-    const float ar = A[d * N + n], aim = Aim[d * N + n];
-    const float at = ar * kLog2e, arev = aim * kInv2Pi;
-    const int64_t cs = Bsz * ND;
-    const int64_t lane = b * ND + n * D + d;
-    const int64_t sl = n * D + d;
-    float st[CP];
+struct CarryComplex {
+    static constexpr int CP = 2 * (1 + K), CS = 1 + K, SS = 1 + K, NP = 2 * (1 + K), GB = K <= 1 ? 4 : (K <= 4 ? 2 : 1);
+    const float ar, aim, at, arev;
+    __device__ __forceinline__ CarryComplex(float re, float im)
+        : ar(re), aim(im), at(re * kLog2e), arev(im * kInv2Pi) {}
+    __device__ __forceinline__ void coef(float (&c)[NP]) const {
+        float s[CS];
 #pragma unroll
-    for (int c = 0; c < CP; ++c) st[c] = state[c * cs + lane];
-    for (int g0 = 0; g0 < G; g0 += GB) {
-        float e[GB][CP], sm[GB][1 + K];
+        for (int i = 0; i < CS; ++i) s[i] = c[i];
+        const float mag = exp2_series(at * s[0]);
+        float cs_, sn_;
+        rot(arev * s[0], cs_, sn_);
+        c[0] = mag * cs_;
+        c[1] = mag * sn_;
 #pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            const int g = g0 + j < G ? g0 + j : G - 1;
-#pragma unroll
-            for (int c = 0; c < CP; ++c) e[j][c] = seg[(((b * G + g) * CP) + c) * ND + sl];
-#pragma unroll
-            for (int c = 0; c <= K; ++c) sm[j][c] = agg_s[((b * G + g) * (1 + K) + c) * D + d];
-        }
-#pragma unroll
-        for (int j = 0; j < GB; ++j) {
-            if (g0 + j >= G) break;
-#pragma unroll
-            for (int c = 0; c < CP; ++c) seg[(((b * G + g0 + j) * CP) + c) * ND + sl] = st[c];
-            const float mag = exp2_series(at * sm[j][0]);
-            float cs_, sn_;
-            rot(arev * sm[j][0], cs_, sn_);
-            const float pr = mag * cs_, pi = mag * sn_;
-            const float hr = st[0], hi = st[1];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                // Q_k = P A S_k
-                const float qr = (pr * ar - pi * aim) * sm[j][1 + k], qi = (pr * aim + pi * ar) * sm[j][1 + k];
-                const float dr = st[2 + 2 * k], di = st[3 + 2 * k];
-                st[2 + 2 * k] = fmaf(pr, dr, -pi * di) + fmaf(qr, hr, -qi * hi) + e[j][2 + 2 * k];
-                st[3 + 2 * k] = fmaf(pr, di, pi * dr) + fmaf(qr, hi, qi * hr) + e[j][3 + 2 * k];
-            }
-            st[0] = fmaf(pr, hr, -pi * hi) + e[j][0];
-            st[1] = fmaf(pr, hi, pi * hr) + e[j][1];
+        for (int k = 0; k < K; ++k) {
+            c[2 + 2 * k] = (c[0] * ar - c[1] * aim) * s[1 + k];
+            c[3 + 2 * k] = (c[0] * aim + c[1] * ar) * s[1 + k];
         }
     }
+    __device__ __forceinline__ void step(float (&st)[CP], const float (&e)[CP], const float (&c)[NP]) const {
+        const float pr = c[0], pi = c[1], hr = st[0], hi = st[1];
 #pragma unroll
-    for (int c = 0; c < CP; ++c) state[c * cs + lane] = st[c];
-}
+        for (int k = 0; k < K; ++k) {
+            const float qr = c[2 + 2 * k], qi = c[3 + 2 * k];
+            const float dr = st[2 + 2 * k], di = st[3 + 2 * k];
+            st[2 + 2 * k] = fmaf(pr, dr, -pi * di) + fmaf(qr, hr, -qi * hi) + e[2 + 2 * k];
+            st[3 + 2 * k] = fmaf(pr, di, pi * dr) + fmaf(qr, hi, qi * hr) + e[3 + 2 * k];
+        }
+        st[0] = fmaf(pr, hr, -pi * hi) + e[0];
+        st[1] = fmaf(pr, hi, pi * hr) + e[1];
+    }
+};
 
 // ---------------------------------------------------------------- state in/out
 // state [comp][B][N][D] <-> h [B][D][N], dh [K][B][D][N].
@@ -3360,30 +3403,48 @@ struct Launcher {
     // the dispatch below only reports whether a kernel exists for the plan.
     bool dry = false;
 
+    // Channel splits of a projection launch.  Up to 32 columns the sum over
+    // channels is a sum of ranges of kProjRange channels: with few blocks (one
+    // per 128 rows and source, fewer than two per CU) each range gets a block
+    // of its own, its records in the other half of the double buffer, which a
+    // call of one host block does not use.  A block walks its channels 32 at
+    // a time, one memory latency each (1.3 us): 64 rows of 1536 channels took
+    // 61 us in one range and take 16 in six with their sum.
     template <int NC>
     void proj_nc(int64_t t0, int64_t len, int buf, hipStream_t ps) {
         if (dry) return;
         float *dst = bc_buf(buf);
-        const int S = q.ksplit;
-        dim3 grid((unsigned)((len + kProjTM - 1) / kProjTM * S), (unsigned)(1 + q.KP), (unsigned)q.B);
+        constexpr bool kRanges = NC <= 32;
+        const int64_t tiles = (len + kProjTM - 1) / kProjTM;
+        int S = q.ksplit, per = 1;
+        int64_t dchunk = q.dchunk, rst = kRanges ? kProjRange / 32 : q.dchunk;
         float *part = (float *)(ws + q.ws.part);
-        const int64_t pstride = (int64_t)(q.ws.bc_half / sizeof(float));
+        int64_t pstride = (int64_t)(q.ws.bc_half / sizeof(float));
+        const int nr = (int)((q.D + kProjRange - 1) / kProjRange);
+        if (kRanges && nr > 1 && q.n_chunks == 1 && tiles * (1 + q.KP) * q.B < 512 && len * (nr - 1) <= q.chunk_len) {
+            per = (int)((q.dchunk + kProjRange - 1) / kProjRange);
+            S = nr;
+            dchunk = kProjRange;
+            part = bc_buf(buf ^ 1);
+            pstride = q.B * len * q.R;
+        }
+        dim3 grid((unsigned)(tiles * S), (unsigned)(1 + q.KP), (unsigned)q.B);
         {
             Timed tm(0, ps, !q.noalloc);
             if (q.groups > 1)
                 hipLaunchKernelGGL((k_proj<NC, InT, true>), grid, dim3(kThreads), 0, ps, x, dx, p.W_B, p.W_C, p.b_B,
-                                   p.b_C, dst, q.B, q.L, q.D, (int)q.KP, t0, len, q.chunk_len, (int)q.N, S,
-                                   q.dchunk, part, pstride);
+                                   p.b_C, dst, q.B, q.L, q.D, (int)q.KP, t0, len, q.chunk_len, (int)q.N, S, dchunk,
+                                   rst, part, pstride);
             else
                 hipLaunchKernelGGL((k_proj<NC, InT, false>), grid, dim3(kThreads), 0, ps, x, dx, p.W_B, p.W_C,
                                    p.b_B, p.b_C, dst, q.B, q.L, q.D, (int)q.KP, t0, len, q.chunk_len, (int)q.N, S,
-                                   q.dchunk, part, pstride);
+                                   dchunk, rst, part, pstride);
         }
         if (S > 1) {
-            const int64_t n = q.B * q.chunk_len * q.R;
             Timed tm(0, ps, !q.noalloc);
-            hipLaunchKernelGGL(k_psum, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, ps, dst,
-                               (const float *)part, pstride, S, n);
+            hipLaunchKernelGGL(k_psum, dim3((unsigned)((len * q.R + kThreads - 1) / kThreads), (unsigned)q.B),
+                               dim3(kThreads), 0, ps, dst, (const float *)part, pstride, S, per, len, q.chunk_len,
+                               q.R, (int)q.N, (int)q.KP, p.b_B, p.b_C);
         }
     }
 
@@ -3439,6 +3500,15 @@ struct Launcher {
         }
     }
 
+    // Composes the G segments of the host block.
+    template <class P>
+    void carry(const float *Aim, int G) {
+        const int w = (G + P::GB - 1) / P::GB;
+        hipLaunchKernelGGL((k_carry_t<P>), dim3((unsigned)((q.N * q.D + 63) / 64), (unsigned)q.B),
+                           dim3(64 * (w < kCarryWaves ? w : kCarryWaves)), 0, st, p.A, Aim,
+                           agg_h(), (const float *)agg_s(), state(), q.B, q.D, q.N, G);
+    }
+
     template <int NT, int NS, int K, int VAR = 0>
     void scans(int64_t t0, int64_t len) {
         if (dry) return;
@@ -3463,10 +3533,8 @@ struct Launcher {
                                agg_h(), agg_s(), q.B, q.L, q.D, t0, len, q.chunk_len, (int64_t)q.seg, G, vr);
         }
         {
-            const int64_t lanes = q.B * ND;
             Timed tm(2, st, !q.noalloc);
-            hipLaunchKernelGGL((k_carry<K>), dim3((unsigned)((lanes + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                               st, p.A, agg_h(), agg_s(), state(), q.B, q.D, q.N, G);
+            carry<CarryFirst<K>>((const float *)nullptr, G);
         }
         {
             Timed tm(3, st, !q.noalloc);
@@ -3562,10 +3630,8 @@ struct Launcher {
                                q.chunk_len, (int64_t)q.seg, G);
         }
         {
-            const int64_t lanes = q.B * ND;
             Timed tm(2, st, !q.noalloc);
-            hipLaunchKernelGGL(k_carry2, dim3((unsigned)((lanes + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                               p.A, agg_h(), agg_s(), state(), q.B, q.D, q.N, G);
+            carry<CarrySecond>((const float *)nullptr, G);
         }
         {
             Timed tm(3, st, !q.noalloc);
@@ -3609,10 +3675,8 @@ struct Launcher {
                                q.L, q.D, t0, len, q.chunk_len, (int64_t)q.seg, G, (const float *)nullptr, 0);
         }
         {
-            const int64_t lanes = q.B * ND;
             Timed tm(2, st, !q.noalloc);
-            hipLaunchKernelGGL((k_ccarry<K>), dim3((unsigned)((lanes + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                               st, p.A, p.A_im, agg_h(), (const float *)agg_s(), state(), q.B, q.D, q.N, G);
+            carry<CarryComplex<K>>(p.A_im, G);
         }
         {
             Timed tm(3, st, !q.noalloc);
@@ -3697,8 +3761,7 @@ struct Launcher {
         const int64_t lanes = q.B * ND;
         {
             Timed tm(2, st, !q.noalloc);
-            hipLaunchKernelGGL(k_pcarry<DLT>, dim3((unsigned)((lanes + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                               st, p.A, agg_h(), agg_s(), state(), q.B, q.D, q.N, G);
+            carry<CarryParam<DLT>>((const float *)nullptr, G);
         }
         // The rescan leaves its per-channel partials in components 1..3 of
         // agg_s (the carry has consumed what the aggregate pass left there).
