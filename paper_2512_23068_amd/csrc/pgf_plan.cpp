@@ -26,6 +26,14 @@ constexpr int kMaxChunkSegs = 4096;
 // is a multiple of this has no partly filled last round.
 constexpr int64_t kResidentBlocks = 1024;
 constexpr int64_t kSimds = 1024;
+// Default segment length: 256 steps where a segment column (every channel of
+// one segment) fills many waves, shorter where it fills few, so that sequences
+// of ten thousand steps still give the GPU several waves per SIMD (it never
+// depends on L).  Shorter segments cost traffic: each adds its state planes
+// four times (written by the aggregate pass, read and written by the carry,
+// read by the output pass).  One direction at B = 1, D = 1536, N = 16 (24
+// waves a column), L = 8192 / 131072, in us: 256 steps 290 / 2190, 128 steps
+// 200 / 2220.  With more than two state planes 256 holds down to 16 waves.
 constexpr int64_t kDefaultSeg = 256;
 constexpr int64_t kMaxChunkLen = int64_t(1) << 18;
 // Workspace caps (of 288 GB of HBM): large enough that the benchmarked
@@ -135,6 +143,10 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
         // Sequential when one segment column already gives every SIMD a wave
         // (a block is 4 waves; an MI355X has 1024 SIMDs).
         seg = (nblk * 4 >= kSimds) ? 0 : kDefaultSeg;
+        if (seg) {
+            const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 4 : 1);
+            seg = waves >= 64 ? 256 : (waves >= 16 ? 128 : (waves >= 8 ? 64 : (waves >= 4 ? 32 : 16)));
+        }
     }
     // Kernels address one host block with 32-bit element offsets.
     constexpr int64_t kMaxBlockElems = int64_t(1) << 30;
@@ -162,7 +174,9 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
         const size_t wcap = ws_cap ? ws_cap : (rank ? kLowRankWorkspaceCap : kWorkspaceCap);
         const int64_t cap = std::max<int64_t>(1, (int64_t)(wcap / per_seg));
         const int64_t period = kResidentBlocks / gcd64(nblk, kResidentBlocks);
-        const int64_t want = (3 * kResidentBlocks + nblk - 1) / nblk;
+        // (counted in 256-step segments, so that shorter ones do not shorten
+        // the host block)
+        const int64_t want = (3 * kResidentBlocks + nblk - 1) / nblk * (seg < 256 ? 256 / seg : 1);
         cs = (want + period - 1) / period * period;
         if (cs > cap) cs = cap >= period ? cap / period * period : cap;
         cs = std::min<int64_t>(cs, kMaxChunkLen / seg);
