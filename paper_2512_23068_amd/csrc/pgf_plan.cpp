@@ -228,9 +228,8 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
     if ((double)K * B * H * (double)L * DV > 9.0e18 / 16) return PGF_ERR_UNSUPPORTED;
     LaPlan q{};
     q.B = B; q.H = H; q.L = L; q.DK = DK; q.DV = DV; q.K = K; q.BH = B * H;
-    // Scan blocks of one segment column, counted in 256-thread units (a
-    // block holds 64 value columns and DK/16 waves).
-    const int64_t nblk = (q.BH * DV / 64 * (DK / 16) + 3) / 4;
+    // Scan blocks of one segment column (four waves: 64 value columns of a head).
+    const int64_t nblk = q.BH * DV / 64;
     int64_t seg;
     if (p->seg_len == -1) {
         seg = 0;
@@ -238,7 +237,10 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
         if (p->seg_len < 16 || p->seg_len > kMaxSeg || !is_pow2(p->seg_len)) return PGF_ERR_INVALID_ARG;
         seg = p->seg_len;
     } else {
-        seg = (nblk * 4 >= kSimds) ? 0 : 128;
+        // 256 steps from 16 blocks a column on (each segment's state, DK x DV
+        // and its tangents, is written and read four times), shorter with
+        // fewer so that short sequences still fill the GPU.
+        seg = (nblk * 4 >= kSimds) ? 0 : (nblk >= 16 ? 256 : (nblk >= 8 ? 128 : (nblk >= 4 ? 64 : 32)));
     }
     if (p->chunk_segs < 0 || p->chunk_segs > kMaxChunkSegs) return PGF_ERR_INVALID_ARG;
     // Per-step offsets of one host block stay below 2^30 elements.
@@ -256,12 +258,11 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
         q.chunk_len = cs * seg;
         q.chunk_segs = (int)cs;
     } else {
-        // At least three rounds of resident blocks per launch, bounded by
+        // At least eight rounds of resident blocks per launch, bounded by
         // a workspace cap of 1 GiB.
-        const size_t per_seg = (size_t)q.BH * (1 + K) * ((size_t)DK * DV + DK) * f +
-                               (size_t)q.BH * seg * (1 + K) * DK * f;
+        const size_t per_seg = (size_t)q.BH * (1 + K) * ((size_t)DK * DV + DK) * f;
         const int64_t cap = std::max<int64_t>(1, (int64_t)(kLaWorkspaceCap / per_seg));
-        cs = (3 * kResidentBlocks + nblk - 1) / nblk;
+        cs = (8 * kResidentBlocks + nblk - 1) / nblk;
         cs = std::min<int64_t>(std::min<int64_t>(cs, cap), kMaxChunkSegs);
         cs = std::min<int64_t>(cs, kMaxChunkLen / seg);
         cs = std::max<int64_t>(cs, 1);
@@ -274,7 +275,6 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
     const size_t comp = (size_t)(1 + K);
     size_t off = 0;
     q.state = off; off = align256(off + comp * q.BH * DK * DV * f);
-    q.rec = off;   off = align256(off + (size_t)q.BH * q.chunk_len * (1 + K) * DK * f);
     const size_t G = seg ? (size_t)q.chunk_segs : 1;
     q.agg_h = off; off = align256(off + (size_t)q.BH * G * comp * DK * DV * f);
     q.agg_s = off; off = align256(off + (size_t)q.BH * G * comp * DK * f);

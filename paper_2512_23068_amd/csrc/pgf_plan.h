@@ -71,7 +71,6 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap = 0);
 // Decaying linear attention.  Workspace sections (256-byte aligned):
 //   state [(1+K)][BH][DK][DV]      state carried between host blocks (the
 //                                  layout of S and dS in the ABI)
-//   rec   [BH][Tc][(1+K)][DK]      per-step alpha = exp(g) and alpha*dg_k
 //   agg_h [BH][G][(1+K)][DK][DV]   segment end states from a zero start,
 //                                  then (in place) the true entry states
 //   agg_s [BH][G][(1+K)][DK]       segment sums of g and dg_k
@@ -80,7 +79,7 @@ struct LaPlan {
     int seg;             // segment length; 0 = sequential evaluation
     int chunk_segs;
     int64_t chunk_len, n_chunks;
-    size_t state, rec, agg_h, agg_s, total;
+    size_t state, agg_h, agg_s, total;
 };
 
 int make_la_plan(const pgf_la_params *p, LaPlan *plan);
