@@ -91,7 +91,7 @@ METRIC = {1: "primal+JVP scan Gtok·ch/s at L=128k", 2: "primal+JVP+second-order
 
 
 COPY_BYTES = 1 << 30
-KERNEL_KIND = {"k_proj": "proj", "k_la_prep": "proj", "k_carry": "carry", "k_pcarry": "carry", "k_la_carry": "carry",
+KERNEL_KIND = {"k_proj": "proj", "k_psum": "proj", "k_carry": "carry", "k_la_carry": "carry",
                "k_gsum": "gsum", "k_state": "state_io", "k_gout": "state_io", "k_fill0": "state_io",
                "k_la_copy": "state_io"}
 SCAN_SRC = "paper_2512_23068_amd/csrc/pgf_scan_kernels.h"
@@ -100,9 +100,9 @@ LA_SRC = "paper_2512_23068_amd/csrc/pgf_la.hip"
 # Sections of the kernel source (delimited by "// ----...---- name" lines)
 # whose code a run of each order executes.
 TRAFFIC_SECTIONS = {
-    1: ("helpers", "variants", "k_proj", "k_scan", "k_scan_sh", "k_carry", "state in/out", "dispatch"),
-    2: ("helpers", "k_proj", "k_scan2", "state in/out", "dispatch"),
-    3: ("helpers", "variants", "k_proj", "parameter flows", "state in/out", "dispatch"),
+    1: ("helpers", "variants", "k_proj", "k_scan", "k_scan_m", "k_scan_sh", "carries", "state in/out", "dispatch"),
+    2: ("helpers", "k_proj", "k_scan2", "carries", "state in/out", "dispatch"),
+    3: ("helpers", "variants", "k_proj", "carries", "parameter flows", "state in/out", "dispatch"),
 }
 
 
@@ -152,7 +152,7 @@ def source_digest(order=1):
 def _kernel_label(name):
     import re
     base = name.split("(")[0].replace("void ", "").strip()
-    if "k_scan" in base or "k_pscan" in base or "k_la_scan" in base:
+    if "k_scan" in base or "k_pscan" in base or "k_la_chunk" in base:
         # the OUT template argument true marks the scan with outputs
         return "scan_out" if re.search(r"[<,]\s*true\s*[,>]", base) else "seg_aggregate"
     for key, lab in KERNEL_KIND.items():
@@ -309,7 +309,7 @@ def setup_ssm(args, np, torch, binding, inputs):
         step=step, tokch=tokch, alg_bytes=alg_bytes, lane_steps=tokch * N,
         flops=tokch * N * (cplx_flops_per_lane_step(K) if args.complex else scan_flops_per_lane_step(K, args.order)),
         payload=payload, plan=plan, metric=METRIC[args.order],
-        kernel={1: "k_scan/k_scan_sh (scan with outputs)", 2: "k_scan2 (scan with outputs)",
+        kernel={1: "k_scan_m/k_scan/k_scan_sh (scan with outputs)", 2: "k_scan2 (scan with outputs)",
                 3: "k_pscan (rescan with outputs and gradient sums)"}[args.order]
         if not args.complex else "k_cscan (scan with outputs)",
         traffic=None if variant else committed_traffic(name, "scan_out", args.order),
@@ -356,7 +356,7 @@ def setup_la(args, np, torch, binding, inputs):
     return Workload(
         step=step, tokch=tokch, alg_bytes=alg_bytes, lane_steps=tokch * DK, flops=tokch * DK * la_flops_per_lane_step(K),
         payload=payload, plan=plan, metric="decaying linear attention primal+JVP Gtok·ch/s",
-        kernel="k_la_scan (scan with outputs)", traffic=committed_traffic(cfg.name, "scan_out", "la"), dtype="f32",
+        kernel="k_la_chunk (scan with outputs)", traffic=committed_traffic(cfg.name, "scan_out", "la"), dtype="f32",
         config={"workload": cfg.name, "batch": B, "heads": H, "seq_len": L, "d_key": DK, "d_value": DV,
                 "n_dirs": K, "parallelism": "single GPU"},
         cpu=(lambda: la_cpu_baseline(cfg, args.cpu_steps)), outputs=(o, do), cfg=cfg)

@@ -120,6 +120,13 @@ __device__ __forceinline__ void exp2_run(float (&v)[4]) {
                  "v_exp_f32 %3, %3\n\ts_setprio 0\n\ts_nop 0"
                  : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
 }
+__device__ __forceinline__ void exp2_run(float (&v)[8]) {
+    asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\t"
+                 "v_exp_f32 %3, %3\n\tv_exp_f32 %4, %4\n\tv_exp_f32 %5, %5\n\tv_exp_f32 %6, %6\n\t"
+                 "v_exp_f32 %7, %7\n\ts_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                   "+v"(v[7]));
+}
 __device__ __forceinline__ void exp2_run(float (&v)[16]) {
     asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\t"
                  "v_exp_f32 %3, %3\n\tv_exp_f32 %4, %4\n\tv_exp_f32 %5, %5\n\tv_exp_f32 %6, %6\n\t"
@@ -2031,11 +2038,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
             float yv = 0.0f, dyv[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) dyv[k] = 0.0f;
+            float av[4];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const int n = ns * NT + i;
                 const float Bn = rec[n];
-                const float a = transition(delta, At[i]);
+                if (i % 4 == 0) {   // the exponentials of four states in one run
+#pragma unroll
+                    for (int j2 = 0; j2 < 4; ++j2) av[j2] = fmaf(delta, At[i + j2], kExp2Lift);
+                    exp2_run(av);
+                }
+                const float a = av[i % 4];
                 const float sv = a * h[i];
                 const float gv = Af[i] * sv;
                 const float hn = fmaf(Bn, u, sv);
@@ -3169,10 +3182,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
                 float yv = 0.0f, dyv[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) dyv[k] = 0.0f;
+                constexpr int ER = NT < 8 ? NT : 8;   // lanes whose exponentials go in one run
+                float ev[ER];
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     const float Bn = rec[i];
-                    const float e = transition(dl2, Ar[i]);
+                    if (i % ER == 0) {
+#pragma unroll
+                        for (int j2 = 0; j2 < ER; ++j2) ev[j2] = fmaf(dl2, Ar[i + j2], kExp2Lift);
+                        exp2_run(ev);
+                    }
+                    const float e = ev[i % ER];
                     float cs, sn;
                     rot(drev * Ai[i], cs, sn);
                     const float ar = e * cs, ai = e * sn;
