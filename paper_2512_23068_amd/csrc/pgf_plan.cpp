@@ -128,7 +128,9 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
     // length; bf16 rows (half the bytes, on the bf16 matrix cores) were
     // faster unsplit.
     q.ksplit = q.in_bf16 ? 1 : (int)std::min<int64_t>(4, (D + 2047) / 2048);
-    q.dchunk = ((D + q.ksplit - 1) / q.ksplit + 255) / 256 * 256;   // whole ranges of k_proj
+    // (up to 32 columns a split is a whole number of k_proj's ranges)
+    const int64_t unit_ch = groups * 2 * N <= 32 ? 256 : 32;
+    q.dchunk = ((D + q.ksplit - 1) / q.ksplit + unit_ch - 1) / unit_ch * unit_ch;
     q.ksplit = (int)((D + q.dchunk - 1) / q.dchunk);
 
     // Blocks of one segment column (every channel, one segment).

@@ -57,7 +57,7 @@ struct Plan {
     int64_t n_chunks;
     int R;               // floats per step in bc: groups * 2N(1+KP)
     int ksplit;          // channel splits S of the projections (1 up to 2048 channels)
-    int64_t dchunk;      // channels per split, a multiple of 256 (kProjRange)
+    int64_t dchunk;      // channels per split, a multiple of 32 (of 256, kProjRange, up to 32 columns)
     int noalloc;         // 1: run every host block in order on the caller's stream
                          // (no helper stream) and record no timing events
     Layout ws;
