@@ -34,6 +34,8 @@ constexpr int64_t kSimds = 1024;
 // read by the output pass).  One direction at B = 1, D = 1536, N = 16 (24
 // waves a column), L = 8192 / 131072, in us: 256 steps 290 / 2190, 128 steps
 // 200 / 2220.  With more than two state planes 256 holds down to 16 waves.
+// Not below 32: with few lanes the carry's chain (about 45 ns a segment) takes
+// over on long sequences (16 channels x 131072 steps: 571 us at 256, 722 at 16).
 constexpr int64_t kDefaultSeg = 256;
 constexpr int64_t kMaxChunkLen = int64_t(1) << 18;
 // Workspace caps (of 288 GB of HBM): large enough that the benchmarked
@@ -147,7 +149,7 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
         seg = (nblk * 4 >= kSimds) ? 0 : kDefaultSeg;
         if (seg) {
             const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 4 : 1);
-            seg = waves >= 64 ? 256 : (waves >= 16 ? 128 : (waves >= 8 ? 64 : (waves >= 4 ? 32 : 16)));
+            seg = waves >= 64 ? 256 : (waves >= 16 ? 128 : (waves >= 3 ? 64 : 32));
         }
     }
     // Kernels address one host block with 32-bit element offsets.

@@ -3429,7 +3429,8 @@ struct Launcher {
     // of its own, its records in the other half of the double buffer, which a
     // call of one host block does not use.  A block walks its channels 32 at
     // a time, one memory latency each (1.3 us): 64 rows of 1536 channels took
-    // 61 us in one range and take 16 in six with their sum.
+    // 61 us in one range and take 19 in six with their sum.  Two ranges gain
+    // less than the extra launch costs.
     template <int NC>
     void proj_nc(int64_t t0, int64_t len, int buf, hipStream_t ps) {
         if (dry) return;
@@ -3441,7 +3442,7 @@ struct Launcher {
         float *part = (float *)(ws + q.ws.part);
         int64_t pstride = (int64_t)(q.ws.bc_half / sizeof(float));
         const int nr = (int)((q.D + kProjRange - 1) / kProjRange);
-        if (kRanges && nr > 1 && q.n_chunks == 1 && tiles * (1 + q.KP) * q.B < 512 && len * (nr - 1) <= q.chunk_len) {
+        if (kRanges && nr > 2 && q.n_chunks == 1 && tiles * (1 + q.KP) * q.B < 512 && len * (nr - 1) <= q.chunk_len) {
             per = (int)((q.dchunk + kProjRange - 1) / kProjRange);
             S = nr;
             dchunk = kProjRange;
