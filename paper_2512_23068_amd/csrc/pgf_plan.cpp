@@ -33,7 +33,7 @@ constexpr int64_t kSimds = 1024;
 // four times (written by the aggregate pass, read and written by the carry,
 // read by the output pass).  One direction at B = 1, D = 1536, N = 16 (24
 // waves a column), L = 8192 / 131072, in us: 256 steps 290 / 2190, 128 steps
-// 200 / 2220.  With more than two state planes 256 holds down to 16 waves.
+// 200 / 2220.  With more than two state planes 256 holds down to 32 waves.
 // Not below 32: with few lanes the carry's chain (about 45 ns a segment) takes
 // over on long sequences (16 channels x 131072 steps: 571 us at 256, 722 at 16).
 constexpr int64_t kDefaultSeg = 256;
@@ -148,7 +148,7 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
         // (a block is 4 waves; an MI355X has 1024 SIMDs).
         seg = (nblk * 4 >= kSimds) ? 0 : kDefaultSeg;
         if (seg) {
-            const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 4 : 1);
+            const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 2 : 1);
             seg = waves >= 64 ? 256 : (waves >= 16 ? 128 : (waves >= 3 ? 64 : 32));
         }
     }
