@@ -2038,17 +2038,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
             float yv = 0.0f, dyv[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) dyv[k] = 0.0f;
-            float av[4];
+            // (four exponentials a step beside some 200 other instructions:
+            // gathering them into a priority run did not change the time)
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const int n = ns * NT + i;
                 const float Bn = rec[n];
-                if (i % 4 == 0) {   // the exponentials of four states in one run
-#pragma unroll
-                    for (int j2 = 0; j2 < 4; ++j2) av[j2] = fmaf(delta, At[i + j2], kExp2Lift);
-                    exp2_run(av);
-                }
-                const float a = av[i % 4];
+                const float a = transition(delta, At[i]);
                 const float sv = a * h[i];
                 const float gv = Af[i] * sv;
                 const float hn = fmaf(Bn, u, sv);
