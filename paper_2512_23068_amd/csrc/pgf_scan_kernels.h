@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "pgf_exp.h"
+#include "pgf_lane.h"
 #include "pgf_plan.h"
 #include "pgf_scan_launch.h"
 #include "pgf_stream.h"
@@ -1377,13 +1378,15 @@ using lanevec = typename LaneVec<NC>::F;
 
 // NC consecutive elements from a uniform base at a 32-bit element offset
 // (element alignment); the row has nd elements from there, or at least NC.
+// Neither the elements from nd on nor the first skip ones are read (a
+// neighbour's value stands in).
 template <int NC>
-__device__ __forceinline__ lanevec<NC> load_lane(const float *__restrict__ base, uint32_t i, int nd) {
+__device__ __forceinline__ lanevec<NC> load_lane(const float *__restrict__ base, uint32_t i, int nd, int skip = 0) {
     const float *p = (const float *)((const char *)base + (size_t)(i * 4u));
-    if (NC == 1 || nd >= NC) return *(const typename LaneVec<NC>::FU *)p;
+    if (NC == 1 || (nd >= NC && skip == 0)) return *(const typename LaneVec<NC>::FU *)p;
     lanevec<NC> v;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) v[j] = p[j < nd ? j : nd - 1];
+    for (int j = 0; j < NC; ++j) v[j] = p[j < skip ? skip : (j < nd ? j : nd - 1)];
     return v;
 }
 template <int NC>
@@ -1406,14 +1409,14 @@ __device__ __forceinline__ lanevec<NC> load_lane(const uint16_t *__restrict__ ba
     return v;
 }
 template <int NC>
-__device__ __forceinline__ void store_lane(float *__restrict__ base, uint32_t i, int nd, lanevec<NC> v) {
+__device__ __forceinline__ void store_lane(float *__restrict__ base, uint32_t i, int nd, int skip, lanevec<NC> v) {
     float *p = (float *)((char *)base + (size_t)(i * 4u));
-    if (NC == 1 || nd >= NC) {
+    if (NC == 1 || (nd >= NC && skip == 0)) {
         *(typename LaneVec<NC>::FU *)p = v;
     } else {
 #pragma unroll
         for (int j = 0; j < NC; ++j)
-            if (j < nd) p[j] = v[j];
+            if (lane_stores(nd, skip, j)) p[j] = v[j];
     }
 }
 
@@ -1467,9 +1470,11 @@ void k_scan_m(
     const int ts = (int)(g * S);             // steps of a host block fit 30 bits
     const int te = (int)(ts + S < len ? ts + S : len);
     if (d0 >= Di || ts >= te) return;
-    // A lane past the last channels computes the last NC again (the same
-    // bits, stored twice).
-    const int cb = Di < NC ? 0 : (d0 + NC * c < Di - NC ? d0 + NC * c : Di - NC);
+    // A lane past the last channels computes the last NC again: within the
+    // wave the same bits, stored twice; channels of the wave before (skip) are
+    // neither read from the state nor stored.
+    const int cb = lane_first(Di, NC, d0, c);
+    const int skip = wave_skip(Di, NC, d0);
     float *step = s_step[wave];
     floatx4 *recs = s_rec[wave];
     float *wb = s_wb[wave] + NC * c;
@@ -1504,12 +1509,12 @@ void k_scan_m(
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t o = (uint32_t)((16 * m + 4 * q + r) * Di + cb);
-                const LV v = load_lane<NC>(ib, o, Di);
+                const LV v = load_lane<NC>(ib, o, Di, skip);
 #pragma unroll
                 for (int j = 0; j < NC; ++j) h[4 * (m * NC + j) + r] = v[j];
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    const LV dv = load_lane<NC>(ib + (1 + k) * ics, o, Di);
+                    const LV dv = load_lane<NC>(ib + (1 + k) * ics, o, Di, skip);
 #pragma unroll
                     for (int j = 0; j < NC; ++j) dh[k][4 * (m * NC + j) + r] = dv[j];
                 }
@@ -1779,9 +1784,9 @@ void k_scan_m(
             }
             if (tb + q < te) {
                 const uint32_t o = (uint32_t)(tb + q) * (uint32_t)Di + (uint32_t)cb;
-                store_lane<NC>(Yb, o, Di, ov[0]);
+                store_lane<NC>(Yb, o, Di, skip, ov[0]);
 #pragma unroll
-                for (int k = 0; k < K; ++k) store_lane<NC>(DYb + k * dxs, o, Di, ov[1 + k]);
+                for (int k = 0; k < K; ++k) store_lane<NC>(DYb + k * dxs, o, Di, skip, ov[1 + k]);
             }
         }
         wave_lds_fence();   // the next tile overwrites the slots
@@ -1796,12 +1801,12 @@ void k_scan_m(
                 LV v;
 #pragma unroll
                 for (int j = 0; j < NC; ++j) v[j] = h[4 * (m * NC + j) + r];
-                store_lane<NC>(dst, o, Di, v);
+                store_lane<NC>(dst, o, Di, skip, v);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
 #pragma unroll
                     for (int j = 0; j < NC; ++j) v[j] = dh[k][4 * (m * NC + j) + r];
-                    store_lane<NC>(dst + (1 + k) * plane, o, Di, v);
+                    store_lane<NC>(dst + (1 + k) * plane, o, Di, skip, v);
                 }
             }
     };
@@ -1826,7 +1831,7 @@ void k_scan_m(
 #pragma unroll
                 for (int j = 0; j < NC; ++j) v[j] += pv[j];
             }
-            store_lane<NC>(agg_s + (base + o) * D, (uint32_t)cb, Di, v);
+            store_lane<NC>(agg_s + (base + o) * D, (uint32_t)cb, Di, skip, v);
         }
     }
 }

@@ -66,3 +66,32 @@ def test_step_edges(L):
 @pytest.mark.parametrize("K", [1, 2])
 def test_variants_at_odd_sizes(drive, act, dres, K):
     _case(16, K, 67, 37, B=2, seg=16, drive=drive, act=act, dres=dres)
+
+
+def _sequential(N, D, L, B, K=1, state=True, bf16=False):
+    what = f"sequential N={N} D={D} L={L} B={B} K={K} bf16={bf16}"
+    print(f"case {what}", flush=True)
+    inp = gu.custom("stiff128k" if bf16 else "mamba130m", batch=B, seqlen=L, d_inner=D, d_state=N, n_dirs=K)
+    r = np.random.default_rng(5)
+    h_in = dh_in = None
+    if state:
+        h_in = r.standard_normal((B, D, N)).astype(np.float32)
+        dh_in = r.standard_normal((K, B, D, N)).astype(np.float32)
+    dev = lambda v: None if v is None else torch.from_numpy(v).to(gu.dev())
+    y, dy, h, dh = gu.run(inp, h_in=dev(h_in), dh_in=dev(dh_in), return_state=True, seg_len=-1)
+    yo, dyo, ho, dho = oracle.scan_jvp(inp["x"], inp["dx"], inp, h_in=h_in, dh_in=dh_in)
+    gu.assert_close(y.cpu().numpy(), dy.cpu().numpy(), yo, dyo, what=what)
+    for got, want, nm in ((h, ho, "h"), (dh, dho, "dh")):
+        e = gu.rel_l2(got.cpu().numpy(), want)
+        assert e <= gu.TOL, (what, nm, e)
+
+
+@pytest.mark.parametrize("N,D", [(16, 65), (16, 66), (16, 67), (16, 257), (16, 259), (32, 33), (32, 129)])
+def test_sequential_last_wave(N, D):
+    """One pass whose exit state replaces its entry state, where the last wave
+    has fewer channels than a lane holds: one step to five, batches of many
+    waves, a host block of a single step."""
+    for L in (1, 2, 5):
+        _sequential(N, D, L, 300)
+    _sequential(N, D, 4097, 2)
+    _sequential(N, D, 7, 40, K=2, bf16=True)
