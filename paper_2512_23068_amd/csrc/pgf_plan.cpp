@@ -143,60 +143,69 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
     } else if (p->seg_len != 0) {
         if (p->seg_len < 16 || p->seg_len > kMaxSeg || !is_pow2(p->seg_len)) return PGF_ERR_INVALID_ARG;
         seg = p->seg_len;
+    } else if (nblk * 4 >= kSimds) {
+        // Sequential: one segment column already gives every SIMD a wave (a
+        // block is 4 waves; an MI355X has 1024 SIMDs).
+        seg = 0;
     } else {
-        // Sequential when one segment column already gives every SIMD a wave
-        // (a block is 4 waves; an MI355X has 1024 SIMDs).
-        seg = (nblk * 4 >= kSimds) ? 0 : kDefaultSeg;
-        if (seg) {
-            const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 2 : 1);
-            seg = waves >= 64 ? 256 : (waves >= 16 ? 128 : (waves >= 3 ? 64 : 32));
-        }
+        const int64_t waves = B * ((D * q.ns + 63) / 64) * (q.comp > 2 ? 2 : 1);
+        seg = waves >= 64 ? kDefaultSeg : (waves >= 16 ? 128 : (waves >= 3 ? 64 : 32));
     }
-    // Kernels address one host block with 32-bit element offsets.
+    // Kernels address one host block with 32-bit element offsets.  A given
+    // chunk_segs with the default segment length is bounded as segments of
+    // kDefaultSeg steps would be, whichever length was chosen.
     constexpr int64_t kMaxBlockElems = int64_t(1) << 30;
-    int64_t cs;
     if (p->chunk_segs < 0 || p->chunk_segs > kMaxChunkSegs) return PGF_ERR_INVALID_ARG;
     const int64_t unit = seg ? seg : kSeqChunk;
-    if (unit * D > kMaxBlockElems) return PGF_ERR_UNSUPPORTED;
-    const int64_t cs_max = kMaxBlockElems / (unit * D);
-    if (p->chunk_segs > cs_max) return PGF_ERR_INVALID_ARG;
+    const int64_t given_unit = seg && p->seg_len == 0 ? kDefaultSeg : unit;
+    if (given_unit * D > kMaxBlockElems) return PGF_ERR_UNSUPPORTED;
+    if (p->chunk_segs > kMaxBlockElems / (given_unit * D)) return PGF_ERR_INVALID_ARG;
+
+    const size_t f = sizeof(float);
+    const size_t comp = (size_t)q.comp;
+    // Sections that do not grow with the host block, and the others per segment.
+    const size_t state_bytes = comp * B * N * D * f;
+    const size_t gacc_bytes = order == 3 ? (3 * (size_t)B * N * D + 3 * (size_t)B * D) * f : 0;
+    int64_t cs;
     if (seg == 0) {
-        cs = p->chunk_segs ? p->chunk_segs : 1;
-        q.chunk_len = cs * kSeqChunk;
-        q.chunk_segs = 1;
+        q.chunk_len = (p->chunk_segs ? p->chunk_segs : 1) * kSeqChunk;
         cs = 1;
     } else if (p->chunk_segs) {
         cs = p->chunk_segs;
         q.chunk_len = cs * seg;
-        q.chunk_segs = (int)cs;
     } else {
         // At least three rounds of resident blocks per launch, rounded to a
-        // whole number of rounds when the workspace allows it.
-        const size_t per_seg = (size_t)B * q.comp * (size_t)(N * D + D) * sizeof(float) +
-                               (size_t)(1 + q.ksplit) * B * seg * q.R * sizeof(float) +
-                               (size_t)(1 + K) * B * seg * (size_t)(rank ? q.rc + D : 0) * sizeof(float);
-        const size_t wcap = ws_cap ? ws_cap : (rank ? kLowRankWorkspaceCap : kWorkspaceCap);
+        // whole number of rounds when the workspace allows it.  A given cap
+        // (the static scratch) holds for the whole workspace, the library's
+        // own for what grows with the host block.
+        const size_t per_seg = (size_t)B * comp * (size_t)(N * D + D) * f +
+                               (size_t)(1 + q.ksplit) * B * seg * q.R * f +
+                               (size_t)(1 + K) * B * seg * (size_t)(rank ? q.rc + D : 0) * f;
+        size_t wcap = ws_cap ? ws_cap : (rank ? kLowRankWorkspaceCap : kWorkspaceCap);
+        if (ws_cap) {
+            const size_t fixed = state_bytes + gacc_bytes + 16 * 256;   // and the sections' alignment
+            wcap = wcap > fixed ? wcap - fixed : 0;
+        }
         const int64_t cap = std::max<int64_t>(1, (int64_t)(wcap / per_seg));
         const int64_t period = kResidentBlocks / gcd64(nblk, kResidentBlocks);
-        // (counted in 256-step segments, so that shorter ones do not shorten
-        // the host block)
-        const int64_t want = (3 * kResidentBlocks + nblk - 1) / nblk * (seg < 256 ? 256 / seg : 1);
+        // (default segments shorter than kDefaultSeg are counted in segments
+        // of that length, so that they do not shorten the host block)
+        const int64_t want = (3 * kResidentBlocks + nblk - 1) / nblk *
+                             (p->seg_len == 0 && seg < kDefaultSeg ? kDefaultSeg / seg : 1);
         cs = (want + period - 1) / period * period;
         if (cs > cap) cs = cap >= period ? cap / period * period : cap;
         cs = std::min<int64_t>(cs, kMaxChunkLen / seg);
-        cs = std::min<int64_t>(std::min<int64_t>(cs, kMaxChunkSegs), cs_max);
+        cs = std::min<int64_t>(std::min<int64_t>(cs, kMaxChunkSegs), kMaxBlockElems / (unit * D));
         cs = std::max<int64_t>(cs, 1);
         q.chunk_len = cs * seg;
-        q.chunk_segs = (int)cs;
     }
+    q.chunk_segs = (int)cs;
     q.seg = (int)seg;
     q.n_chunks = (L + q.chunk_len - 1) / q.chunk_len;
 
-    const size_t f = sizeof(float);
-    const size_t comp = (size_t)q.comp;
     Layout w{};
     size_t off = 0;
-    w.state = off; off = align256(off + comp * B * N * D * f);
+    w.state = off; off = align256(off + state_bytes);
     w.bc = off;
     w.bc_half = align256((size_t)B * q.chunk_len * q.R * f);
     off += 2 * w.bc_half;
@@ -210,7 +219,7 @@ int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap) {
         w.agg_h = w.agg_s = off;
     }
     w.gacc = off;
-    if (order == 3) off = align256(off + (3 * (size_t)B * N * D + 3 * (size_t)B * D) * f);
+    off = align256(off + gacc_bytes);
     w.lr = off;
     if (rank) off = align256(off + (size_t)(1 + K) * B * q.chunk_len * q.rc * f);
     w.dt = off;

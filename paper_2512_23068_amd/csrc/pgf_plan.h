@@ -63,9 +63,10 @@ struct Plan {
     Layout ws;
 };
 
-// Validates the size fields and fills *plan.  ws_cap bounds the workspace
-// that the default host-block size may take (0: the library's caps); an
-// explicit chunk_segs is not bounded.  Returns PGF_OK or an error.
+// Validates the size fields and fills *plan.  ws_cap bounds the whole
+// workspace that the default host-block size may take, down to one segment
+// (0: the library's caps); an explicit chunk_segs is not bounded.  Returns
+// PGF_OK or an error.
 int make_plan(const pgf_params *p, Plan *plan, size_t ws_cap = 0);
 
 // Decaying linear attention.  Workspace sections (256-byte aligned):

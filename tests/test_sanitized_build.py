@@ -36,6 +36,17 @@ def test_planner_under_sanitizers(tmp_path):
     assert "0 failures" in r.stdout and "ERROR" not in r.stderr and "runtime error" not in r.stderr
 
 
+def test_planner_limits_under_sanitizers(tmp_path):
+    exe = str(tmp_path / "limits_driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", *SAN, "-o", exe,
+                    os.path.join(ROOT, "tests", "sanitize", "limits_driver.cpp"),
+                    os.path.join(ROOT, "paper_2512_23068_amd", "csrc", "pgf_plan.cpp")], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(r.stdout[-3000:], r.stderr)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr
+    assert "0 failures" in r.stdout and "ERROR" not in r.stderr and "runtime error" not in r.stderr
+
+
 def test_oracle_pins_under_sanitizers(tmp_path):
     lib = str(tmp_path / "liboracle_san.so")
     oracle.build(out=lib, extra=tuple(SAN))
