@@ -3,17 +3,17 @@
 //
 // The state of one (batch, head) is a dk x dv matrix S.  A block owns 64 value
 // columns of one head and takes a segment in chunks of 16 steps.  Within a
-// chunk, with G_t the sum of g up to and including step t (per key) and
-//   Q_t = q_t e^{G_t},  K_s = k_s e^{-G_s},
-// the steps are products of small matrices, on the f32 matrix cores:
-//   o_t = Q_t S + sum_{s<=t} (Q_t . K_s) v_s,   S' = e^{G_16} (S + sum_s K_s v_s^T)
-// and the tangent along (dq, dk, dv, dg) is their product rule with
-//   dQ_t = (dq_t + q_t dG_t) e^{G_t},  dK_s = (dk_s - k_s dG_s) e^{-G_s},
-//   dS' = e^{G_16} dS~ + dG_16 S',  S~ the bracket above.
-// Where a chunk's |G| exceeds kMaxG, or a scaled operand or a value is not
-// finite, its steps are taken one at a time by the same code (decay the state,
-// then the products of one step), which needs no e^{-G} and keeps a value
-// that is not finite from the steps before it.
+// chunk, with G_t the sum of g up to and including step t (per key), the steps
+// are products of small matrices, on the f32 matrix cores:
+//   o_t = (q_t e^{G_t}) S + sum_{s<=t} w_st v_s,  w_st = sum_keys q_t k_s e^{G_t - G_s},
+//   S' = e^{G_16} S + sum_s (k_s e^{G_16 - G_s}) v_s^T,
+// and the tangent along (dq, dk, dv, dg) is their product rule.  Every factor
+// e^{..} and every difference of dG is formed from the steps between its ends
+// alone (k_la_chunk), so a decay that underflows loses only what it has
+// forgotten and no term cancels another.  A chunk with a value that is not
+// finite, or so large or small that a product of q and k could leave the range
+// of f32, is taken one step at a time by the same code (decay, k v, q S),
+// which keeps a value that is not finite from the steps before it.
 //
 // Kernels, per host block of steps [t0, t0+len):
 //   k_la_chunk<false>  zero-start segment aggregates (end states) and the
@@ -54,9 +54,17 @@ __device__ __forceinline__ float exp_acc(float v) {
 
 // ---------------------------------------------------------------- scan
 constexpr int kChunk = 16;       // steps per chunk
-constexpr float kMaxG = 60.0f;   // e^60 = 1e26: products with |k|, |q| below 1e12 stay finite
+// Limits of the chunk form (beyond them a chunk goes step by step).  Its
+// products associate as (q k) v where the recurrence takes q (k v): with
+// |q|, |k| (and their tangents) up to kMaxQK, |dg| up to kMaxDg and a growth
+// (positive g) of e^4 at most, the sums over 64 keys stay below 2^127; values
+// so small that q k could leave the normal range while v brings the outputs
+// back into it are kept out by kMinQ and kMinK (of a wave's largest value).
+constexpr float kMaxQK = 0x1p40f, kMaxDg = 0x1p30f, kMaxGrow = 4.0f / kChunk;
+constexpr float kMinQ = 0x1p-80f, kMinK = 0x1p-40f;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -75,19 +83,56 @@ __device__ __forceinline__ void st(float *base, uint32_t i, float x) {
 // stores of the last one stay in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Sums of two values over lane halves at once: rows of 32 (16) lanes of a and
+// b are paired, so that lanes of even 32-halves (rows of 16) hold a's sum over
+// the pair and those of odd ones b's.
+__device__ __forceinline__ float pair_sum32(float a, float b) {
+    const uintx2 r = __builtin_bit_cast(
+        uintx2, __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float pair_sum16(float a, float b) {
+    const uintx2 r = __builtin_bit_cast(
+        uintx2, __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Sum over a row of 16 lanes, in every lane of the row.
+template <int ROT>
+__device__ __forceinline__ float add_ror(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + ROT, 0xF,
+                                                                     0xF, false));
+}
+__device__ __forceinline__ float row_sum(float v) { return add_ror<1>(add_ror<2>(add_ror<4>(add_ror<8>(v)))); }
+
 // v_mfma_f32_16x16x4f32: lane (q, c) = (l/16, l%16) supplies A[c][q] and
 // B[q][c] and receives D[4q + r][c] in accumulator r.  Wave w owns columns
 // 16w .. 16w+15 of the block and every key: S[kt][r] is key 16kt + 4q + r of
 // column c, so that each S[kt][r] is the B operand of the products with Q
-// (k index q <-> key 16kt + 4q + r) as it lies.  The 16 x 16 products K_s . Q_t
-// are formed by every wave with s in the rows, whose accumulators are then
-// the A operand of the product with v (s = 4q + r), without a transposition.
-// Thread (tg, key) prepares SPT consecutive steps of one key: K and Q as rows
-// [t][key] and K also as [key][t] for the update of S.
+// (k index q <-> key 16kt + 4q + r) as it lies.  Thread (tg, key) prepares SPT
+// consecutive steps of one key.
 //
-// Bound by the f32 matrix cores in the output pass (120 instructions of 32
+// The weight of step s in the output of a later step t of the chunk is
+// e^{g_{s+1} + .. + g_t} per key.  It is never formed as e^{G_t} e^{-G_s}:
+// e^{-G} leaves the range of f32 for decays that models have, and the
+// tangent's dG_t - dG_s cancels where one step decays strongly.  Instead the
+// pairs are cut by the highest bit L in which s and t differ (8, 4, 2, 1):
+// with c the first step of t's half of their block of 2L,
+//   e^{..} = e^{g_{s+1} + .. + g_{c-1}} (with k_s)  e^{g_c + .. + g_t} (with q_t)
+// and every factor, for S and the state's update too, is a product of the
+// steps' own e^g (one exponential each) along a tree, every dG a sum of the
+// steps' dg.  At each level a step is either a k (bit clear) or a q (bit set),
+// so two levels fill the 16 rows and 16 columns of one product: rows and
+// columns 0-7 hold level 8 (2), 8-15 level 4 (1), the quarters on the
+// diagonal count.  q_t . k_t is summed over the keys by the vector unit.
+// The parts of each key tile meet in sP, whose entry [16 (s/4) + t][s%4] is
+// weight (s, t): the A operand of the product with v, without a transposition.
+//
+// Bound by the f32 matrix cores in the output pass (132 instructions of 32
 // cycles per wave and chunk at dk = 64, one direction) and by memory in the
-// aggregate pass (48).
+// aggregate pass (48).  At 32 heads x 32768 steps, dk = dv = 64, one direction,
+// a call takes 1.33 ms and errs by 4.6e-7; a single reference per chunk
+// (e^{G_t} e^{-G_s}, 120 instructions) took 1.20 ms and lost what is said
+// above, the recurrence on the vector unit 2.38 ms at 6.7e-7.
 template <int DK, int K, bool OUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !OUT ? 4 : 2))) void k_la_chunk(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
@@ -99,22 +144,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
     constexpr int NG = 256 / DK;         // thread groups over the steps of a chunk
     constexpr int SPT = kChunk / NG;     // steps per thread
     constexpr int P = DK + 4, PT = kChunk + 4;
-    constexpr int NQ = OUT ? 1 + K : 1;
-    __shared__ __align__(16) float sQ[NQ][OUT ? kChunk : 1][P];
-    __shared__ __align__(16) float sK[NQ][OUT ? kChunk : 1][P];
-    __shared__ __align__(16) float sKT[1 + K][DK][PT];
-    __shared__ __align__(16) float sEnd[1 + K][DK];     // e^{G_16}, dG_16
-    __shared__ float sTot[1 + K][NG][DK];
+    constexpr int O = 1 + K, NQ = OUT ? O : 1, RQ = OUT ? kChunk : 1;
+    // With two directions at dk = 64 the two products share their operands'
+    // LDS, one after the other, so that two blocks fit a CU.
+    constexpr int SETS = K == 2 && DK == 64 ? 1 : 2;
+    __shared__ __align__(16) float sQ[NQ][RQ][P];
+    __shared__ __align__(16) float sLv[2][OUT ? SETS : 1][NQ][RQ][P];   // [k | q] of a level pair
+    __shared__ floatx4 sP[NQ][OUT ? KT : 1][OUT ? 64 : 1];
+    __shared__ __align__(16) float sKT[O][DK][PT];
+    __shared__ __align__(16) float sEnd[O][DK];         // e^{G_16}, dG_16
+    __shared__ float sTot[O][NG][DK];                   // products of e^g, sums of dg
+    __shared__ float sSum[NG][DK];                      // sums of g
     __shared__ int sBad[2];
-    // K_s . Q_t and its tangents: with four key tiles each wave forms the part
-    // of one tile and all add the four (36 of 156 products saved, for a barrier)
-    constexpr bool PART = OUT && KT == 4;
-    __shared__ floatx4 sP[PART ? 1 + K : 1][PART ? 4 : 1][PART ? 64 : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid % 64, c = lane % 16, qd = lane / 16;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int key = tid % DK, tg = tid / DK;
+    const int key = tid % DK, tg = DK == 64 ? w : tid / DK;
     const int64_t groups = DV / 64;
     const int64_t bh = blockIdx.x / groups;
     const int64_t cg = blockIdx.x % groups;
@@ -145,6 +191,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
             for (int kk = 0; kk < K; ++kk) dS[kk][kt][r] = OUT ? ld(ib + (1 + kk) * ics, e) : 0.0f;
         }
     if (tid < 2) sBad[tid] = 0;
+    if constexpr (OUT) {
+        // weights of s > t stay zero
+        for (int i = tid; i < NQ * KT * 64; i += 256) (&sP[0][0][0])[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
 
     // key-side inputs of this thread's steps and the value rows 4qd + m
     float rg[SPT], rk[SPT], rq[SPT], rdg[K][SPT], rdk[K][SPT], rdq[K][SPT], vn[4], dvn[K][4];
@@ -174,23 +224,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
             for (int kk = 0; kk < K; ++kk) dvn[kk][m] = live ? ld(dvb + kk * dvs, e) : 0.0f;
         }
     };
-    // This thread's rows of the operands from step j's scaled values.
-    auto put = [&](int j, float kv, const float (&dkv)[K], float qv, const float (&dqv)[K]) {
-        const int t = tg * SPT + j;
-        sKT[0][key][t] = kv;
-        if constexpr (OUT) {
-            sK[0][t][key] = kv;
-            sQ[0][t][key] = qv;
-        }
-#pragma unroll
-        for (int kk = 0; kk < K; ++kk) {
-            sKT[1 + kk][key][t] = dkv[kk];
-            if constexpr (OUT) {
-                sK[1 + kk][t][key] = dkv[kk];
-                sQ[1 + kk][t][key] = dqv[kk];
-            }
-        }
-    };
     // S <- e S, dS <- e dS + dG S' for the decay in sEnd
     auto decay = [&]() {
 #pragma unroll
@@ -206,38 +239,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
             }
         }
     };
-    // The products of one staged chunk: outputs of its rows (the values of
-    // row 4qd + r, stored for rows lo <= row < hi of the chunk), then S~.
-    auto products = [&](int tb, int lo, int hi, const float (&vv)[4], const float (&dvv)[K][4]) {
+    // o += Q S and its tangents
+    auto read_out = [&](floatx4 &ov, floatx4 (&dov)[K]) {
         if constexpr (OUT) {
-            floatx4 ov = {0.0f, 0.0f, 0.0f, 0.0f}, dov[K], pv = ov, dpv[K];
-#pragma unroll
-            for (int kk = 0; kk < K; ++kk) dov[kk] = dpv[kk] = pv;
-            auto inner = [&](int kt) {
-                const floatx4 qa = *(const floatx4 *)&sQ[0][c][16 * kt + 4 * qd];
-                const floatx4 ka = *(const floatx4 *)&sK[0][c][16 * kt + 4 * qd];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) pv = mfma4(ka[r], qa[r], pv);
-#pragma unroll
-                for (int kk = 0; kk < K; ++kk) {
-                    const floatx4 dqa = *(const floatx4 *)&sQ[1 + kk][c][16 * kt + 4 * qd];
-                    const floatx4 dka = *(const floatx4 *)&sK[1 + kk][c][16 * kt + 4 * qd];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        dpv[kk] = mfma4(dka[r], qa[r], dpv[kk]);
-                        dpv[kk] = mfma4(ka[r], dqa[r], dpv[kk]);
-                    }
-                }
-            };
-            if constexpr (PART) {
-                inner(w);
-                sP[0][w][lane] = pv;
-#pragma unroll
-                for (int kk = 0; kk < K; ++kk) sP[1 + kk][w][lane] = dpv[kk];
-            }
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
-                if constexpr (!PART) inner(kt);
                 const floatx4 qa = *(const floatx4 *)&sQ[0][c][16 * kt + 4 * qd];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) ov = mfma4(qa[r], Sm[kt][r], ov);
@@ -251,52 +257,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
                     }
                 }
             }
-            if constexpr (PART) {
-                lds_barrier();
-                pv = sP[0][0][lane];
-#pragma unroll
-                for (int kk = 0; kk < K; ++kk) dpv[kk] = sP[1 + kk][0][lane];
-#pragma unroll
-                for (int h = 1; h < 4; ++h) {
-                    const floatx4 pw = sP[0][h][lane];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) pv[r] += pw[r];
-#pragma unroll
-                    for (int kk = 0; kk < K; ++kk) {
-                        const floatx4 dpw = sP[1 + kk][h][lane];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) dpv[kk][r] += dpw[r];
-                    }
-                }
-            }
-            // pv[r] = K_s . Q_t, s = 4qd + r, t = c: only s <= t counts
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool in = 4 * qd + r <= c;
-                pv[r] = in ? pv[r] : 0.0f;
-#pragma unroll
-                for (int kk = 0; kk < K; ++kk) dpv[kk][r] = in ? dpv[kk][r] : 0.0f;
-            }
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                ov = mfma4(pv[m], vv[m], ov);
-#pragma unroll
-                for (int kk = 0; kk < K; ++kk) {
-                    dov[kk] = mfma4(dpv[kk][m], vv[m], dov[kk]);
-                    dov[kk] = mfma4(pv[m], dvv[kk][m], dov[kk]);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int t = 4 * qd + r;
-                if (t >= lo && t < hi && tb + t < te) {
-                    const uint32_t e = (uint32_t)(tb + t) * DVu + cl;
-                    st(ob, e, ov[r]);
-#pragma unroll
-                    for (int kk = 0; kk < K; ++kk) st(dob + kk * dvs, e, dov[kk][r]);
-                }
-            }
         }
+    };
+    // S += K v and its tangents
+    auto update = [&](const float (&vv)[4], const float (&dvv)[K][4]) {
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             const floatx4 ka = *(const floatx4 *)&sKT[0][16 * kt + c][4 * qd];
@@ -311,6 +275,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
             }
 #pragma unroll
             for (int m = 0; m < 4; ++m) Sm[kt] = mfma4(ka[m], vv[m], Sm[kt]);
+        }
+    };
+    // stores rows lo <= row < hi of the chunk
+    auto put_out = [&](int tb, int lo, int hi, floatx4 ov, const floatx4 (&dov)[K]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int t = 4 * qd + r;
+            if (t >= lo && t < hi && tb + t < te) {
+                const uint32_t e = (uint32_t)(tb + t) * DVu + cl;
+                st(ob, e, ov[r]);
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) st(dob + kk * dvs, e, dov[kk][r]);
+            }
+        }
+    };
+    // The weights of one level pair (set 0: levels 8 and 4, set 1: 2 and 1)
+    // over one key tile, left in sP.
+    auto weights = [&](int set, int kt) {
+        if constexpr (OUT) {
+            const float (*ks)[kChunk][P] = sLv[0][SETS == 2 ? set : 0], (*qs)[kChunk][P] = sLv[1][SETS == 2 ? set : 0];
+            const floatx4 ka = *(const floatx4 *)&ks[0][c][16 * kt + 4 * qd];
+            const floatx4 qa = *(const floatx4 *)&qs[0][c][16 * kt + 4 * qd];
+            floatx4 pv[O];
+#pragma unroll
+            for (int cc = 0; cc < O; ++cc) pv[cc] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pv[0] = mfma4(ka[r], qa[r], pv[0]);
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                const floatx4 dka = *(const floatx4 *)&ks[1 + kk][c][16 * kt + 4 * qd];
+                const floatx4 dqa = *(const floatx4 *)&qs[1 + kk][c][16 * kt + 4 * qd];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    pv[1 + kk] = mfma4(dka[r], qa[r], pv[1 + kk]);
+                    pv[1 + kk] = mfma4(ka[r], dqa[r], pv[1 + kk]);
+                }
+            }
+            // row 4qd + r is a k, column c a q of the packed rows
+            const int h = c & 7;
+#pragma unroll
+            for (int cc = 0; cc < O; ++cc) {
+                floatx4 *sp = sP[cc][kt];
+                const floatx4 p = pv[cc];
+                if (set == 0) {
+                    if (qd < 2) {
+                        if (c < 8) sp[16 * qd + 8 + c] = p;                        // s = 4qd + r, t = 8 + c
+                    } else if (c / 4 == qd) {
+                        sp[32 * (qd - 2) + 8 * (qd - 2) + 4 + (c & 3)] = p;        // s = 8(qd-2) + r
+                    }
+                } else if (qd < 2) {
+                    if (c / 4 == qd) {                                             // s = 4(c/2) + {0, 1}
+                        float *e = (float *)&sp[16 * (c / 2) + 4 * (c / 2) + 2 + (c & 1)];
+                        e[0] = c & 2 ? p[2] : p[0];
+                        e[1] = c & 2 ? p[3] : p[1];
+                    }
+                } else if (c / 4 == qd) {                                          // s = 2h, t = 2h + 1
+                    float *e = (float *)&sp[16 * (h / 2) + 2 * h + 1];
+                    e[2 * (h & 1)] = h & 2 ? (h & 1 ? p[3] : p[2]) : (h & 1 ? p[1] : p[0]);
+                }
+            }
         }
     };
 
@@ -332,88 +356,282 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 1 && !
                 chk = fmaf(dvv[kk][m], 0.0f, chk);
             }
         }
-        // G and dG within this thread's steps, then the steps before them
-        float Gt[SPT], dGt[K][SPT];
+        // this thread's decays, their product and the sums of dg
+        float a[SPT], grow = 0.0f, mag = 0.0f, mdg = 0.0f, qmax = 0.0f, kmax = 0.0f;
 #pragma unroll
         for (int j = 0; j < SPT; ++j) {
-            Gt[j] = j ? Gt[j - 1] + rg[j] : rg[j];
-#pragma unroll
-            for (int kk = 0; kk < K; ++kk) dGt[kk][j] = j ? dGt[kk][j - 1] + rdg[kk][j] : rdg[kk][j];
-        }
-        if constexpr (!OUT) {
-            sg += Gt[SPT - 1];
-#pragma unroll
-            for (int kk = 0; kk < K; ++kk) sdg[kk] += dGt[kk][SPT - 1];
-        }
-        sTot[0][tg][key] = Gt[SPT - 1];
-#pragma unroll
-        for (int kk = 0; kk < K; ++kk) sTot[1 + kk][tg][key] = dGt[kk][SPT - 1];
-        lds_barrier();          // also: every wave has left the last chunk's operands
-        float g0 = 0.0f, dg0[K];
-#pragma unroll
-        for (int kk = 0; kk < K; ++kk) dg0[kk] = 0.0f;
-#pragma unroll
-        for (int h = 0; h < NG - 1; ++h) {
-            const bool before = h < tg;
-            g0 += before ? sTot[0][h][key] : 0.0f;
-#pragma unroll
-            for (int kk = 0; kk < K; ++kk) dg0[kk] += before ? sTot[1 + kk][h][key] : 0.0f;
-        }
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < SPT; ++j) {
-            const float Gj = g0 + Gt[j];
-            bad |= !(fabsf(Gj) <= kMaxG);
-            const float ei = exp_acc(-Gj), eq = OUT || j == SPT - 1 ? exp_acc(Gj) : 0.0f;
-            const float kv = rk[j] * ei;
-            const float qv = OUT ? rq[j] * eq : 0.0f;
-            float dkv[K], dqv[K];
-            chk = fmaf(kv, 0.0f, fmaf(qv, 0.0f, chk));
+            a[j] = exp_acc(rg[j]);
+            chk = fmaf(a[j], 0.0f, chk);
+            grow += fmaxf(rg[j], 0.0f);
+            mag += fabsf(rk[j]);
+            kmax = fmaxf(kmax, fabsf(rk[j]));
+            if constexpr (OUT) {
+                mag += fabsf(rq[j]);
+                qmax = fmaxf(qmax, fabsf(rq[j]));
+            }
 #pragma unroll
             for (int kk = 0; kk < K; ++kk) {
-                const float dGj = dg0[kk] + dGt[kk][j];
-                dkv[kk] = fmaf(-rk[j], dGj, rdk[kk][j]) * ei;
-                dqv[kk] = OUT ? fmaf(rq[j], dGj, rdq[kk][j]) * eq : 0.0f;
-                chk = fmaf(dkv[kk], 0.0f, fmaf(dqv[kk], 0.0f, chk));
-                if (j == SPT - 1 && tg == NG - 1) sEnd[1 + kk][key] = dGj;
+                mdg += fabsf(rdg[kk][j]);
+                mag += fabsf(rdk[kk][j]);
+                kmax = fmaxf(kmax, fabsf(rdk[kk][j]));
+                if constexpr (OUT) {
+                    mag += fabsf(rdq[kk][j]);
+                    qmax = fmaxf(qmax, fabsf(rdq[kk][j]));
+                }
             }
-            if (j == SPT - 1 && tg == NG - 1) sEnd[0][key] = eq;
-            put(j, kv, dkv, qv, dqv);
+            if constexpr (!OUT) {
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) sdg[kk] += rdg[kk][j];
+            }
         }
-        if (bad || !(chk == 0.0f)) sBad[buf] = 1;
+        float gsum = rg[0];      // of the chunk, once the other threads' are added
+        {
+            float T = a[0], D[K];
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) D[kk] = rdg[kk][0];
+#pragma unroll
+            for (int j = 1; j < SPT; ++j) {
+                T *= a[j];
+                gsum += rg[j];
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) D[kk] += rdg[kk][j];
+            }
+            sTot[0][tg][key] = T;
+            sSum[tg][key] = gsum;
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) sTot[1 + kk][tg][key] = D[kk];
+        }
+        if constexpr (!OUT) sg += gsum;
+        bool bad = !(mag <= kMaxQK) || !(mdg <= kMaxDg) || !(grow <= kMaxGrow * SPT) || !(chk == 0.0f);
+        if constexpr (OUT) {
+            // a wave whose q (k) are all tiny, not all zero
+            const auto any = [](bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; };
+            bad |= (any(qmax > 0.0f) && !any(qmax >= kMinQ)) || (any(kmax > 0.0f) && !any(kmax >= kMinK));
+        }
+        lds_barrier();          // also: every wave has left the last chunk's operands
+        if (bad) sBad[buf] = 1;
+
+        // Per step: the decay (p, inclusive) and dg from the start of its block
+        // of 2^i steps, and (s, exclusive) to its end, doubling the block.
+        float pf[SPT], sf[SPT], pd[K][SPT], sd[K][SPT];
+        float lf[4][SPT], ld_[4][K][SPT];     // each level's factor: p of a q, s of a k
+#pragma unroll
+        for (int j = 0; j < SPT; ++j) {
+            pf[j] = a[j];
+            sf[j] = 1.0f;
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                pd[kk][j] = rdg[kk][j];
+                sd[kk][j] = 0.0f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int Lv = 1 << i;
+            if (Lv < SPT) {
+                float tf[SPT], td[K][SPT];    // a block's totals, at its last step
+#pragma unroll
+                for (int j = 0; j < SPT; ++j) {
+                    tf[j] = pf[j];
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk) td[kk][j] = pd[kk][j];
+                }
+#pragma unroll
+                for (int j = 0; j < SPT; ++j) {
+                    const bool up = (j & Lv) != 0;
+                    const int x = up ? (j & ~(Lv - 1)) - 1 : (j | (2 * Lv - 1));   // last step of the other half
+                    lf[i][j] = up ? pf[j] : sf[j];
+                    (up ? pf[j] : sf[j]) *= tf[x];
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk) {
+                        ld_[i][kk][j] = up ? pd[kk][j] : sd[kk][j];
+                        (up ? pd[kk][j] : sd[kk][j]) += td[kk][x];
+                    }
+                }
+            } else {
+                const int m = Lv / SPT;       // thread groups of a half
+                const bool up = (tg & m) != 0;
+                const int h0 = (tg ^ m) & ~(m - 1);
+                float T = sTot[0][h0][key], D[K];
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) D[kk] = sTot[1 + kk][h0][key];
+#pragma unroll
+                for (int h = 1; h < m; ++h) {
+                    T *= sTot[0][h0 + h][key];
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk) D[kk] += sTot[1 + kk][h0 + h][key];
+                }
+#pragma unroll
+                for (int j = 0; j < SPT; ++j) {
+                    lf[i][j] = up ? pf[j] : sf[j];
+                    pf[j] = up ? pf[j] * T : pf[j];
+                    sf[j] = up ? sf[j] : sf[j] * T;
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk) {
+                        ld_[i][kk][j] = up ? pd[kk][j] : sd[kk][j];
+                        pd[kk][j] = up ? pd[kk][j] + D[kk] : pd[kk][j];
+                        sd[kk][j] = up ? sd[kk][j] : sd[kk][j] + D[kk];
+                    }
+                }
+            }
+        }
+        // the operands of level i
+        auto stage = [&](int i) {
+            if constexpr (OUT) {
+                const int Lv = 1 << i;
+#pragma unroll
+                for (int j = 0; j < SPT; ++j) {
+                    const int t = tg * SPT + j;
+                    const bool up = Lv < SPT ? (j & Lv) != 0 : (tg & (Lv / SPT)) != 0;
+                    const int row = (t & (Lv - 1)) + t / (2 * Lv) * Lv + (i % 2 == 0 ? 8 : 0);
+                    float *dst = &sLv[up][SETS == 2 && i < 2 ? 1 : 0][0][row][key];
+                    const float x = up ? rq[j] : rk[j];
+                    dst[0] = x * lf[i][j];
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk)
+                        dst[(1 + kk) * kChunk * P] =
+                            fmaf(x, ld_[i][kk][j], up ? rdq[kk][j] : rdk[kk][j]) * lf[i][j];
+                }
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < SPT; ++j) {
+            const int t = tg * SPT + j;
+            sKT[0][key][t] = rk[j] * sf[j];
+            if constexpr (OUT) sQ[0][t][key] = rq[j] * pf[j];
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                sKT[1 + kk][key][t] = fmaf(rk[j], sd[kk][j], rdk[kk][j]) * sf[j];
+                if constexpr (OUT) sQ[1 + kk][t][key] = fmaf(rq[j], pd[kk][j], rdq[kk][j]) * pf[j];
+            }
+        }
+        if (tg == NG - 1) {
+            // The state's own decay is one exponential of the sum of g: over a
+            // long memory 16 rounded factors a chunk add up (errors at the
+            // RWKV sizes 1.1e-6 with their product, 4.5e-7 with this).
+#pragma unroll
+            for (int h = NG - 2; h >= 0; --h) gsum += sSum[h][key];
+            sEnd[0][key] = exp_acc(gsum);
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) sEnd[1 + kk][key] = pd[kk][SPT - 1];
+        }
+        if constexpr (OUT) {
+            stage(3);
+            stage(2);
+            if (SETS == 2) {
+                stage(1);
+                stage(0);
+            }
+            // the weights of s = t: sums over the keys, four steps a wave, the
+            // rows of 16 lanes holding one step each
+#pragma unroll
+            for (int cc = 0; cc < O; ++cc) {
+                float z[SPT];
+#pragma unroll
+                for (int j = 0; j < SPT; ++j)
+                    z[j] = cc == 0 ? rq[j] * rk[j]
+                                   : fmaf(rdq[cc ? cc - 1 : 0][j], rk[j], rq[j] * rdk[cc ? cc - 1 : 0][j]);
+                float sum;
+                int t;
+                if constexpr (SPT == 4) {
+                    sum = pair_sum16(pair_sum32(z[0], z[1]), pair_sum32(z[2], z[3]));
+                    t = 4 * w + ((qd & 1) << 1 | qd >> 1);
+                } else if constexpr (SPT == 2) {
+                    sum = pair_sum16(z[0], z[1]);
+                    t = 4 * w + qd;
+                } else {
+                    sum = z[0];
+                    t = 4 * w + qd;
+                }
+                sum = row_sum(sum);
+                if (c == 0) ((float *)&sP[cc][0][16 * w + t])[t & 3] = sum;
+            }
+        }
         lds_barrier();
         if (__builtin_amdgcn_readfirstlane(sBad[buf]) == 0) {
-            fetch(tb + kChunk);
-            products(tb, 0, kChunk, vv, dvv);
+            floatx4 ov = {0.0f, 0.0f, 0.0f, 0.0f}, dov[K];
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) dov[kk] = ov;
+            if constexpr (OUT) {
+                if constexpr (SETS == 1) {
+                    weights(0, w);
+                    lds_barrier();
+                    stage(1);
+                    stage(0);
+                    fetch(tb + kChunk);
+                    lds_barrier();
+                    weights(1, w);
+                } else {
+                    fetch(tb + kChunk);
+                    if constexpr (KT == 4) {
+                        weights(0, w);
+                        weights(1, w);
+                    } else if (w < 2 * KT) {
+                        weights(w / KT, w % KT);
+                    }
+                }
+                read_out(ov, dov);
+                lds_barrier();
+                floatx4 pv[O];
+#pragma unroll
+                for (int cc = 0; cc < O; ++cc) {
+                    pv[cc] = sP[cc][0][lane];
+#pragma unroll
+                    for (int kt = 1; kt < KT; ++kt) {
+                        const floatx4 pw = sP[cc][kt][lane];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) pv[cc][r] += pw[r];
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    ov = mfma4(pv[0][m], vv[m], ov);
+#pragma unroll
+                    for (int kk = 0; kk < K; ++kk) {
+                        dov[kk] = mfma4(pv[1 + kk][m], vv[m], dov[kk]);
+                        dov[kk] = mfma4(pv[0][m], dvv[kk][m], dov[kk]);
+                    }
+                }
+                put_out(tb, 0, kChunk, ov, dov);
+            } else {
+                fetch(tb + kChunk);
+            }
             decay();
+            update(vv, dvv);
         } else {
-            // one step at a time: decay by the step, then its products alone
+            // one step at a time, as the recurrence has it: decay, k v, q S
             for (int sub = 0; sub < kChunk; ++sub) {
                 lds_barrier();
 #pragma unroll
                 for (int j = 0; j < SPT; ++j) {
-                    const bool on = tg * SPT + j == sub;
-                    float dkv[K], dqv[K];
+                    const int t = tg * SPT + j;
+                    const bool on = t == sub;
+                    sKT[0][key][t] = on ? rk[j] : 0.0f;
+                    if constexpr (OUT) sQ[0][t][key] = rq[j];
+                    if (on) sEnd[0][key] = exp_acc(rg[j]);
 #pragma unroll
                     for (int kk = 0; kk < K; ++kk) {
-                        dkv[kk] = on ? rdk[kk][j] : 0.0f;
-                        dqv[kk] = OUT && on ? rdq[kk][j] : 0.0f;
+                        sKT[1 + kk][key][t] = on ? rdk[kk][j] : 0.0f;
+                        if constexpr (OUT) sQ[1 + kk][t][key] = rdq[kk][j];
                         if (on) sEnd[1 + kk][key] = rdg[kk][j];
                     }
-                    if (on) sEnd[0][key] = exp_acc(rg[j]);
-                    put(j, on ? rk[j] : 0.0f, dkv, OUT && on ? rq[j] : 0.0f, dqv);
                 }
-                float vs[4], dvs[K][4];
+                float vs[4], dvs_[K][4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     const bool on = 4 * qd + m == sub;
                     vs[m] = on ? vv[m] : 0.0f;
 #pragma unroll
-                    for (int kk = 0; kk < K; ++kk) dvs[kk][m] = on ? dvv[kk][m] : 0.0f;
+                    for (int kk = 0; kk < K; ++kk) dvs_[kk][m] = on ? dvv[kk][m] : 0.0f;
                 }
                 lds_barrier();
                 decay();
-                products(tb, sub, sub + 1, vs, dvs);
+                update(vs, dvs_);
+                floatx4 ov = {0.0f, 0.0f, 0.0f, 0.0f}, dov[K];
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) dov[kk] = ov;
+                read_out(ov, dov);
+                if constexpr (OUT) put_out(tb, sub, sub + 1, ov, dov);
             }
             fetch(tb + kChunk);
         }
