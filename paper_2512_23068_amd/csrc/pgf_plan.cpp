@@ -252,8 +252,10 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
     } else {
         // 256 steps from 16 blocks a column on (each segment's state, DK x DV
         // and its tangents, is written and read four times), shorter with
-        // fewer so that short sequences still fill the GPU.
-        seg = (nblk * 4 >= kSimds) ? 0 : (nblk >= 16 ? 256 : (nblk >= 8 ? 128 : (nblk >= 4 ? 64 : 32)));
+        // fewer so that short sequences still fill the GPU.  Not below 64: one
+        // head, dk = 64, 1024 / 16384 / 131072 steps, in us, 32-step segments
+        // 38 / 87 / 575, 64 44 / 69 / 368, 128 69 / 79 / 261.
+        seg = (nblk * 4 >= kSimds) ? 0 : (nblk >= 16 ? 256 : (nblk >= 8 ? 128 : 64));
     }
     if (p->chunk_segs < 0 || p->chunk_segs > kMaxChunkSegs) return PGF_ERR_INVALID_ARG;
     // Per-step offsets of one host block stay below 2^30 elements.

@@ -138,3 +138,20 @@ def test_infinite_query_stays_with_its_outputs():
     o = _run(inp, seg_len=-1)[0]
     assert torch.isposinf(o[:, :, 37]).all() and torch.isfinite(o[:, :, :37]).all()
     assert torch.isfinite(o[:, :, 38:]).all()
+
+
+@pytest.mark.parametrize("K,segments", [(1, (2, 7, 8, 9, 63, 64, 65, 130)), (2, (3, 4, 5, 31, 32, 33, 70))])
+def test_carry_rounds(K, segments):
+    """Segments around the runs that one wave of the carry takes, and around a
+    round of all its waves, with entry and exit states."""
+    r = np.random.default_rng(8)
+    S_in = r.standard_normal((1, 2, 16, 64)).astype(np.float32)
+    dS_in = r.standard_normal((K, 1, 2, 16, 64)).astype(np.float32)
+    for n in segments:
+        inp = _inputs(16, K, 16 * n - 5)
+        print(f"case la carry K={K} segments={n}", flush=True)
+        ref = oracle.la_scan_jvp(*[inp[m] for m in NAMES], state=(S_in, dS_in))
+        dev = [torch.from_numpy(v).to(gu.dev()) for v in (S_in, dS_in)]
+        for got, want, nm in zip(_run(inp, seg_len=16, S_in=dev[0], dS_in=dev[1]), ref, ("o", "do", "S", "dS")):
+            e = gu.rel_l2(got.cpu().numpy(), want)
+            assert e <= gu.TOL, (K, n, nm, e)
