@@ -249,42 +249,55 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
     } else if (p->seg_len != 0) {
         if (p->seg_len < 16 || p->seg_len > kMaxSeg || !is_pow2(p->seg_len)) return PGF_ERR_INVALID_ARG;
         seg = p->seg_len;
+    } else if (nblk * 4 >= kSimds) {
+        // Sequential from one wave per SIMD on: half the work in one wave each
+        // against all of it in several.  256 heads of 2048 steps, dv = 64, in
+        // us, sequential / 128-step segments: dk = 16 305 / 286, 32 380 / 422,
+        // 64 584 / 713; 512 heads 402 / 559, 556 / 831, 890 / 1417.
+        seg = 0;
     } else {
         // 256 steps from 16 blocks a column on (each segment's state, DK x DV
         // and its tangents, is written and read four times), shorter with
         // fewer so that short sequences still fill the GPU.  Not below 64: one
         // head, dk = 64, 1024 / 16384 / 131072 steps, in us, 32-step segments
         // 38 / 87 / 575, 64 44 / 69 / 368, 128 69 / 79 / 261.
-        seg = (nblk * 4 >= kSimds) ? 0 : (nblk >= 16 ? 256 : (nblk >= 8 ? 128 : 64));
+        seg = nblk >= 16 ? 256 : (nblk >= 8 ? 128 : 64);
     }
     if (p->chunk_segs < 0 || p->chunk_segs > kMaxChunkSegs) return PGF_ERR_INVALID_ARG;
-    // Per-step offsets of one host block stay below 2^30 elements.
+    // Per-step offsets of one host block stay below 2^30 elements.  A given
+    // chunk_segs beside the default segment length is bounded as segments of
+    // 128 steps would be (or as a sequential block, where the blocks of 4096
+    // state entries fill the SIMDs), whichever length was chosen, and the
+    // block is cut to the bound if the chosen one is longer.
     constexpr int64_t kMaxBlockElems = int64_t(1) << 30;
+    const int64_t width = std::max(DK, DV);
     const int64_t unit = seg ? seg : kSeqChunk;
-    if (unit * std::max(DK, DV) > kMaxBlockElems) return PGF_ERR_UNSUPPORTED;
+    if (unit * width > kMaxBlockElems) return PGF_ERR_UNSUPPORTED;
+    const int64_t entry_blocks = (nblk * (DK / 16) + 3) / 4;
+    const int64_t given_unit = p->seg_len == 0 ? (entry_blocks * 4 >= kSimds ? kSeqChunk : 128) : unit;
+    if (p->chunk_segs * given_unit * width > kMaxBlockElems) return PGF_ERR_INVALID_ARG;
     const size_t f = sizeof(float);
     int64_t cs;
-    if (seg == 0) {
-        cs = p->chunk_segs ? p->chunk_segs : 1;
-        q.chunk_len = cs * kSeqChunk;
-        q.chunk_segs = 1;
-    } else if (p->chunk_segs) {
-        cs = p->chunk_segs;
-        q.chunk_len = cs * seg;
-        q.chunk_segs = (int)cs;
+    if (p->chunk_segs) {
+        cs = std::min<int64_t>(p->chunk_segs, kMaxBlockElems / (unit * width));
+    } else if (seg == 0) {
+        cs = 1;
     } else {
-        // At least eight rounds of resident blocks per launch, bounded by
-        // a workspace cap of 1 GiB.
+        // At least eight rounds of resident blocks per launch, bounded by a
+        // workspace cap of 1 GiB; with a given segment length three, counted
+        // in blocks of 4096 state entries.
+        const int64_t rounds = p->seg_len == 0 ? 8 : 3;
+        const int64_t blocks = p->seg_len == 0 ? nblk : entry_blocks;
         const size_t per_seg = (size_t)q.BH * (1 + K) * ((size_t)DK * DV + DK) * f;
         const int64_t cap = std::max<int64_t>(1, (int64_t)(kLaWorkspaceCap / per_seg));
-        cs = (8 * kResidentBlocks + nblk - 1) / nblk;
+        cs = (rounds * kResidentBlocks + blocks - 1) / blocks;
         cs = std::min<int64_t>(std::min<int64_t>(cs, cap), kMaxChunkSegs);
         cs = std::min<int64_t>(cs, kMaxChunkLen / seg);
         cs = std::max<int64_t>(cs, 1);
-        q.chunk_len = cs * seg;
-        q.chunk_segs = (int)cs;
     }
-    if (q.chunk_len * std::max(DK, DV) > kMaxBlockElems) return PGF_ERR_INVALID_ARG;
+    q.chunk_len = cs * unit;
+    q.chunk_segs = seg ? (int)cs : 1;
+    if (q.chunk_len * width > kMaxBlockElems) return PGF_ERR_INVALID_ARG;
     q.seg = (int)seg;
     q.n_chunks = (L + q.chunk_len - 1) / q.chunk_len;
     const size_t comp = (size_t)(1 + K);

@@ -82,6 +82,31 @@ int main() {
             fail("block of a given segment length", p);
         }
     }
+    // linear attention: a given chunk_segs beside the default segment length is
+    // bounded as 128-step segments (2^30 elements), sequential blocks where
+    // blocks of 4096 state entries fill the GPU, and cut where the chosen
+    // length is longer; a given length keeps three rounds of those blocks
+    const struct { int64_t H, DK, DV; int seg, segs, rc; int64_t len; } la[] = {
+        {1, 16, 64, 0, 4096, PGF_OK, 4096 * 64},    {1, 16, 2048, 0, 4096, PGF_OK, 524288},
+        {1, 16, 4096, 0, 4096, PGF_ERR_INVALID_ARG, 0}, {2, 16, 4096, 0, 1024, PGF_OK, 262144},
+        {6, 16, 4096, 0, 256, PGF_OK, 262144},      {64, 16, 4096, 0, 64, PGF_OK, 262144},
+        {64, 16, 4096, 0, 65, PGF_ERR_INVALID_ARG, 0}, {256, 64, 64, 0, 4, PGF_OK, 16384},
+        {1, 16, 64, 16, 0, PGF_OK, 3072 * 16},      {32, 64, 64, 128, 0, PGF_OK, 96 * 128},
+        {8, 16, 128, 64, 0, PGF_OK, 768 * 64},      {1, 64, 64, 16, 4096, PGF_OK, 4096 * 16},
+    };
+    for (const auto &c : la) {
+        pgf_la_params p;
+        memset(&p, 0, sizeof(p));
+        p.batch = 1; p.heads = c.H; p.seqlen = 131072; p.d_key = c.DK; p.d_value = c.DV; p.n_dirs = 1;
+        p.seg_len = c.seg; p.chunk_segs = c.segs;
+        pgf::LaPlan q;
+        const int rc = pgf::make_la_plan(&p, &q);
+        if (rc != c.rc || (rc == PGF_OK && q.chunk_len != c.len)) {
+            printf("linear attention: H %ld DK %ld DV %ld seg %d chunk_segs %d: rc %d block %ld\n", (long)c.H,
+                   (long)c.DK, (long)c.DV, c.seg, c.segs, rc, rc == PGF_OK ? (long)q.chunk_len : 0L);
+            ++failures;
+        }
+    }
     printf("%ld plans fit their cap, %d failures\n", fitted, failures);
     return failures ? 1 : 0;
 }
