@@ -1339,7 +1339,7 @@ void k_scan(
 // one 0.91 and 1.22, 1.24 and 1.83, 1.63 and 1.86.  Leaving out the matrix
 // updates, the exponentials, the discretisation or the loads and stores
 // saves 0.22, 0.10, 0.11 and 0.18 ms of the 1.22: no one of them dominates.
-// One direction runs four waves per SIMD (126 VGPRs, 37 KB of LDS a block);
+// One direction runs four waves per SIMD (128 VGPRs, 37 KB of LDS a block);
 // two directions and the ZOH drive two.
 //
 // Everything a wave shares goes through its own LDS slice (no block barrier;
@@ -1429,7 +1429,8 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 template <int M, int K, bool OUT, typename InT, int VAR = 0>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(K == 1 && (VAR & kZoh) == 0 ? 4 : 2)))
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(K == 1 && (VAR & kZoh) == 0 ? 4 : 2)))
 void k_scan_m(
     const InT *__restrict__ x, const InT *__restrict__ dx, const float *__restrict__ A,
     const float *__restrict__ w_delta, const float *__restrict__ b_delta, const float *__restrict__ bc,
@@ -1570,7 +1571,14 @@ void k_scan_m(
     };
     fetch(ts);
 
-    for (int tb = ts; tb < te; tb += TT) {
+    // One tile; GUARD for a segment's last one with fewer than TT steps, whose
+    // missing steps are skipped (their lanes repeat the last step's inputs).
+    // Every tile is guarded where the unguarded copy costs a wave per SIMD (64
+    // states, two directions, aggregate pass: 180 VGPRs against 163; a call of
+    // 8192 steps x 1536 channels takes 0.837 and 0.808 ms).
+    constexpr bool SPLIT = !(M == 4 && K == 2 && !OUT);
+    auto tile = [&](const int tb, auto guard) __attribute__((always_inline)) {
+        constexpr bool GUARD = decltype(guard)::value;
         // --- this lane's step (tb + q) of its channels
         const LV xv = xn;
         LV dxv[K], delta, dD[K];
@@ -1588,17 +1596,7 @@ void k_scan_m(
 #pragma unroll
                 for (int j = 0; j < NC; ++j) dD[k][j] = sw[j] * dxv[k][j];
         }
-        if (tb + TT > te) {
-            // a step past the segment leaves the state exactly as it is
-            // (Abar = 1, no drive); its outputs are not stored
-            const bool live = tb + q < te;
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                delta[j] = live ? delta[j] : 0.0f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) dD[k][j] = live ? dD[k][j] : 0.0f;
-            }
-        }
+        const bool live = !GUARD || tb + q < te;
         {
             // scalars of the step, one row of CH channels each: Euler
             // Delta log2(e), u, dDelta_k, p_k; ZOH Delta, x, dDelta_k, dx_k
@@ -1608,11 +1606,11 @@ void k_scan_m(
             for (int j = 0; j < NC; ++j) {
                 f0[j] = ZOH ? delta[j] : delta[j] * kLog2e;
                 f1[j] = ZOH ? xv[j] : delta[j] * xv[j];
-                if constexpr (!OUT) sD[j] += delta[j];
+                if constexpr (!OUT) sD[j] += live ? delta[j] : 0.0f;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     f3[k][j] = ZOH ? dxv[k][j] : fmaf(dD[k][j], xv[j], delta[j] * dxv[k][j]);
-                    if constexpr (!OUT) sdD[k][j] = add_rounded(sdD[k][j], dD[k][j]);
+                    if constexpr (!OUT) sdD[k][j] = add_rounded(sdD[k][j], live ? dD[k][j] : 0.0f);
                 }
             }
             *(LV *)sc = f0;
@@ -1626,7 +1624,7 @@ void k_scan_m(
 #pragma unroll
         for (int i = 0; i < RV; ++i)
             if (RU % 64 == 0 || lane + 64 * i < RU) recs[lane + 64 * i] = rn[i];
-        fetch(tb + TT);
+        if constexpr (!GUARD || !SPLIT) fetch(tb + TT);
         wave_lds_fence();
 
         // --- the steps; each reads the next one's scalars and mfma operands
@@ -1647,10 +1645,12 @@ void k_scan_m(
 #pragma unroll
             for (int k = 0; k < K; ++k) ndB[k] = ra[(1 + k) * N];
         };
-        if constexpr (AHEAD) read_step(0);
+        constexpr bool RA = AHEAD && !GUARD;
+        if constexpr (RA) read_step(0);
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
-            if constexpr (!AHEAD) read_step(t);
+            if (GUARD && tb + t >= te) continue;
+            if constexpr (!RA) read_step(t);
             const float *rec = (const float *)recs + t * R;
             const LV f0 = n0;
             LV f2[K];
@@ -1662,7 +1662,7 @@ void k_scan_m(
                 f3[k] = n3[k];
                 dBa[k] = ndB[k];
             }
-            if (AHEAD && t + 1 < TT) read_step(t + 1);
+            if (RA && t + 1 < TT) read_step(t + 1);
             floatx16 a;
             {
                 float v[16];
@@ -1782,7 +1782,7 @@ void k_scan_m(
                     }
                 }
             }
-            if (tb + q < te) {
+            if (live) {
                 const uint32_t o = (uint32_t)(tb + q) * (uint32_t)Di + (uint32_t)cb;
                 store_lane<NC>(Yb, o, Di, skip, ov[0]);
 #pragma unroll
@@ -1790,6 +1790,13 @@ void k_scan_m(
             }
         }
         wave_lds_fence();   // the next tile overwrites the slots
+    };
+    int tb = ts;
+    if constexpr (SPLIT) {
+        for (; tb + TT <= te; tb += TT) tile(tb, std::false_type{});
+        if (tb < te) tile(tb, std::true_type{});
+    } else {
+        for (; tb < te; tb += TT) tile(tb, std::true_type{});
     }
 
     auto put_state = [&](float *dst, int64_t plane) {

@@ -95,3 +95,26 @@ def test_sequential_last_wave(N, D):
         _sequential(N, D, L, 300)
     _sequential(N, D, 4097, 2)
     _sequential(N, D, 7, 40, K=2, bf16=True)
+
+
+@pytest.mark.parametrize("N,K,bf16,drive", [(16, 1, False, "euler"), (16, 2, False, "euler"), (16, 1, True, "euler"),
+                                            (16, 1, False, "zoh"), (64, 2, False, "euler"), (32, 1, False, "euler")])
+def test_overflow_at_the_last_step(N, K, bf16, drive):
+    """After zeros a last step that overflows the state of a channel: the exit
+    state is the same wherever in a tile of four steps it falls (steps past the
+    sequence leave a state that is not finite as it is too)."""
+    one = gu.custom("stiff128k" if bf16 else "mamba130m", batch=1, seqlen=1, d_inner=20, d_state=N, n_dirs=K)
+    one["x"][:, 0, 3] = 2.0 ** 100
+    one["w_delta"][3] = 1.0
+    ref = None
+    for L in (4, 1, 2, 3, 5, 6, 7, 8):
+        inp = dict(one)
+        inp["x"] = np.concatenate([np.zeros((1, L - 1, 20), np.float32), one["x"]], 1)
+        inp["dx"] = np.concatenate([np.zeros((K, 1, L - 1, 20), np.float32), one["dx"]], 2)
+        got = gu.run(inp, bf16=bf16, return_state=True, seg_len=-1, drive=drive)[2:]
+        print(f"case overflow N={N} K={K} bf16={bf16} {drive} L={L}", flush=True)
+        ref = ref or got
+        assert not torch.isfinite(ref[0][:, 3]).all()
+        for a, b in zip(got, ref):
+            assert torch.equal(torch.isnan(a), torch.isnan(b)), L
+            assert torch.equal(torch.nan_to_num(a, nan=0.0), torch.nan_to_num(b, nan=0.0)), L
