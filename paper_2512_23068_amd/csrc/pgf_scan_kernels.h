@@ -1075,7 +1075,11 @@ void k_scan(
     const int64_t b = blockIdx.z;
     const int64_t ts = (int64_t)g * S;
     const int64_t te = ts + S < len ? ts + S : len;
-    if (ts >= te) return;
+    // A wave without channels ends here: its threads would compute channel D-1
+    // from the state that the owner's wave may have replaced already (the
+    // sequential evaluation), and store that.
+    const int64_t wave_d = (int64_t)blockIdx.x * DPB + __builtin_amdgcn_readfirstlane(tid / 64) * (64 / NS);
+    if (ts >= te || wave_d >= D) return;
 
     float Af[NT], At[NT], Ai[NT];
 #pragma unroll
@@ -3098,7 +3102,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
     const int64_t b = blockIdx.z;
     const int64_t ts = (int64_t)g * S;
     const int64_t te = ts + S < len ? ts + S : len;
-    if (ts >= te) return;
+    const int64_t wave_d =
+        (int64_t)blockIdx.x * (kThreads / NS) + __builtin_amdgcn_readfirstlane(tid / 64) * (64 / NS);
+    if (ts >= te || wave_d >= D) return;   // (a wave without channels, as in k_scan)
 
     // Only A itself is held per lane; the step's scale factors of the
     // exponent (Delta log2 e) and of the angle in revolutions (Delta / 2 pi)

@@ -68,15 +68,20 @@ def test_variants_at_odd_sizes(drive, act, dres, K):
     _case(16, K, 67, 37, B=2, seg=16, drive=drive, act=act, dres=dres)
 
 
-def _sequential(N, D, L, B, K=1, state=True, bf16=False):
-    what = f"sequential N={N} D={D} L={L} B={B} K={K} bf16={bf16}"
+def _sequential(N, D, L, B, K=1, state=True, bf16=False, cplx=False):
+    what = f"sequential N={N} D={D} L={L} B={B} K={K} bf16={bf16} complex={cplx}"
     print(f"case {what}", flush=True)
     inp = gu.custom("stiff128k" if bf16 else "mamba130m", batch=B, seqlen=L, d_inner=D, d_state=N, n_dirs=K)
     r = np.random.default_rng(5)
     h_in = dh_in = None
+    if cplx:
+        inp["A_im"] = r.uniform(-6.0, 6.0, (D, N)).astype(np.float32)
     if state:
-        h_in = r.standard_normal((B, D, N)).astype(np.float32)
-        dh_in = r.standard_normal((K, B, D, N)).astype(np.float32)
+        rs = lambda *s: r.standard_normal(s).astype(np.float32) + (1j * r.standard_normal(s).astype(np.float32)
+                                                                   if cplx else 0)
+        h_in, dh_in = rs(B, D, N), rs(K, B, D, N)
+        if cplx:
+            h_in, dh_in = h_in.astype(np.complex64), dh_in.astype(np.complex64)
     dev = lambda v: None if v is None else torch.from_numpy(v).to(gu.dev())
     y, dy, h, dh = gu.run(inp, h_in=dev(h_in), dh_in=dev(dh_in), return_state=True, seg_len=-1)
     yo, dyo, ho, dho = oracle.scan_jvp(inp["x"], inp["dx"], inp, h_in=h_in, dh_in=dh_in)
@@ -95,6 +100,15 @@ def test_sequential_last_wave(N, D):
         _sequential(N, D, L, 300)
     _sequential(N, D, 4097, 2)
     _sequential(N, D, 7, 40, K=2, bf16=True)
+
+
+@pytest.mark.parametrize("N,K,cplx", [(4, 1, False), (8, 1, False), (8, 2, False), (16, 1, True), (32, 1, True)])
+def test_sequential_waves_without_channels(N, K, cplx):
+    """Blocks with one wave of channels and three without, in one pass whose
+    exit state replaces its entry state."""
+    for D in (1, 63, 257):
+        for L in (1, 2, 5):
+            _sequential(N, D, L, 200, K=K, cplx=cplx)
 
 
 @pytest.mark.parametrize("N,K,bf16,drive", [(16, 1, False, "euler"), (16, 2, False, "euler"), (16, 1, True, "euler"),
