@@ -3013,6 +3013,7 @@ static __global__ __launch_bounds__(kThreads) void k_gout(
 // for long sequences.  Layouts as k_scan with the state split into planes:
 // component c = 2m + part (m = 0 h, 1..K dh_k).
 constexpr float kInv2Pi = 0.159154943091895336f;
+constexpr float kInv2PiLo = 6.42063833e-09f;        // 1/(2 pi) - kInv2Pi
 constexpr float kTwoPiHi = 6.28318548202514648f;   // 2 pi rounded to f32
 constexpr float kTwoPiLo = -1.74845553e-07f;        // 2 pi - kTwoPiHi
 
@@ -3048,6 +3049,18 @@ __device__ __forceinline__ void rot(float rev, float &c, float &s) {
     const float sg = k != 0.0f ? -1.0f : 1.0f;   // k in {-1, 0, 1}
     s = sg * sp;
     c = sg * cp;
+}
+
+// cos and sin of the angle a t (a in radians per unit of t): the revolutions
+// a/(2 pi) t with their rounding kept, the whole ones dropped before it is
+// added.  A segment's angle has tens of revolutions, of which one rounding is
+// 1e-5 of a radian.
+__device__ __forceinline__ void rot_by(float a, float t, float &c, float &s) {
+    const float hi = a * kInv2Pi;
+    const float lo = fmaf(a, kInv2Pi, -hi) + a * kInv2PiLo;
+    const float p = hi * t;
+    const float pl = fmaf(hi, t, -p) + lo * t;
+    rot((p - __builtin_rintf(p)) + pl, c, s);
 }
 
 // The ZOH drive coefficient of a complex lane, e = (Abar - 1)/A = Delta
@@ -3180,7 +3193,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
                 float delta, sw;
                 discretize(xv, w, bd, delta, sw);
                 const float u = delta * xv;
-                const float dl2 = delta * kLog2e, drev = delta * kInv2Pi;
+                // (kInv2Pi alone is 4e-8 low, in the same direction at every step)
+                const float dl2 = delta * kLog2e, drev = fmaf(delta, kInv2Pi, delta * kInv2PiLo);
                 float dD[K], pk[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
@@ -3332,16 +3346,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
 template <int K>
 struct CarryComplex {
     static constexpr int CP = 2 * (1 + K), CS = 1 + K, SS = 1 + K, NP = 2 * (1 + K), GB = K <= 1 ? 4 : (K <= 4 ? 2 : 1);
-    const float ar, aim, at, arev;
-    __device__ __forceinline__ CarryComplex(float re, float im)
-        : ar(re), aim(im), at(re * kLog2e), arev(im * kInv2Pi) {}
+    const float ar, aim, at;
+    __device__ __forceinline__ CarryComplex(float re, float im) : ar(re), aim(im), at(re * kLog2e) {}
     __device__ __forceinline__ void coef(float (&c)[NP]) const {
         float s[CS];
 #pragma unroll
         for (int i = 0; i < CS; ++i) s[i] = c[i];
         const float mag = exp2_series(at * s[0]);
         float cs_, sn_;
-        rot(arev * s[0], cs_, sn_);
+        rot_by(aim, s[0], cs_, sn_);
         c[0] = mag * cs_;
         c[1] = mag * sn_;
 #pragma unroll

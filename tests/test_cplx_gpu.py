@@ -211,3 +211,25 @@ def test_cplx_wide_state_is_the_sum_of_its_halves(drive):
               (h, torch.cat([parts[0][2], parts[1][2]], -1)), (dh, torch.cat([parts[0][3], parts[1][3]], -1)))
     for got, want in checks:
         assert gu.rel_l2(got.cpu().numpy(), want.cpu().numpy()) < 1e-6
+
+
+def test_long_memory_phase_has_no_drift():
+    """S4D-Lin (A = -1/2 + i pi n) over 16384 steps: every step and every
+    segment turns a lane by Delta A_im / (2 pi) revolutions.  With 1/(2 pi) as
+    one f32 (4e-8 low) all of them fall short in the same direction and dy errs
+    by 5.2e-6 (one pass: 4.9e-6); with its low part the roundings are random:
+    3.6e-6 (3.1e-6).  The bound lies between, 20 % from either."""
+    D = 48
+    inp = gu.custom("mamba130m", batch=1, seqlen=16384, d_inner=D, d_state=16, n_dirs=1, dx_kind="normal")
+    r = np.random.default_rng(17)
+    inp["A"] = np.full((D, 16), -0.5, np.float32)
+    inp["A_im"] = np.tile((np.pi * np.arange(16)).astype(np.float32), (D, 1))
+    v = np.exp(np.log(1e-3) + np.log(1e2) * r.random(D))
+    inp["b_delta"] = np.log(np.expm1(v)).astype(np.float32)
+    inp["w_delta"] = r.standard_normal(D).astype(np.float32)
+    for seg in (128, -1):
+        y, dy = gu.run(inp, seg_len=seg)
+        yo, dyo, _, _ = oracle.scan_jvp(inp["x"], inp["dx"], inp)
+        ey, edy = gu.rel_l2(y.cpu().numpy(), yo), gu.rel_l2(dy.cpu().numpy(), dyo)
+        print(f"case long complex memory seg={seg} rel_l2 y={ey:.2e} dy={edy:.2e}", flush=True)
+        assert edy <= 4.3e-6, (seg, edy)
