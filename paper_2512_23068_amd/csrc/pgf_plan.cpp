@@ -303,7 +303,6 @@ int make_la_plan(const pgf_la_params *p, LaPlan *plan) {
     const size_t comp = (size_t)(1 + K);
     size_t off = 0;
     q.state = off; off = align256(off + comp * q.BH * DK * DV * f);
-    q.rec = off;
     const size_t G = seg ? (size_t)q.chunk_segs : 1;
     q.agg_h = off; off = align256(off + (size_t)q.BH * G * comp * DK * DV * f);
     q.agg_s = off; off = align256(off + (size_t)q.BH * G * comp * DK * f);

@@ -80,7 +80,7 @@ struct LaPlan {
     int seg;             // segment length; 0 = sequential evaluation
     int chunk_segs;
     int64_t chunk_len, n_chunks;
-    size_t state, rec, agg_h, agg_s, total;   // rec: end of state (no per-step records are kept)
+    size_t state, agg_h, agg_s, total;
 };
 
 int make_la_plan(const pgf_la_params *p, LaPlan *plan);

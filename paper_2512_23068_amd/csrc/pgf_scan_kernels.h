@@ -1037,17 +1037,17 @@ __global__ __launch_bounds__(kThreads) void k_lowdt(
 }
 
 // ---------------------------------------------------------------- k_scan
-// Grid (ceil(D*NS/256), G, B); thread -> (channel d, state group ns).
+// Grid (ceil(D/256), G, B); thread -> channel d with all its N states.
 // OUT=false: segment aggregate from a zero state.  OUT=true: scan from the
 // entry state at init[b*ibs + g*igs + c*ics + n*D + d] and write y, dy; if
 // end_state is set (sequential evaluation) the exit state is stored there
 // with the same indexing (g = 0).
 // It serves the tilings with fewer than 16 states per thread and one thread
 // per channel (N = 4, 8; k_scan_m has the rest).
-template <int NT, int NS, int K, bool OUT, typename InT, int VAR = 0>
+template <int N, int K, bool OUT, typename InT, int VAR = 0>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(K == 1 && (VAR & kZoh) == 0 && std::is_same<InT, float>::value ? 4
-                                   : (K == 2 && NS == 1 && (OUT || (VAR & kZoh) == 0) ? 3 : 1))))
+                                   : (K == 2 && (OUT || (VAR & kZoh) == 0) ? 3 : 1))))
 void k_scan(
     const InT *__restrict__ x, const InT *__restrict__ dx, const float *__restrict__ A,
     const float *__restrict__ w_delta, const float *__restrict__ b_delta, const float *__restrict__ bc,
@@ -1055,10 +1055,7 @@ void k_scan(
     float *__restrict__ y, float *__restrict__ dy, float *__restrict__ end_state,
     float *__restrict__ agg_h, float *__restrict__ agg_s,
     int64_t Bsz, int64_t L, int64_t D, int64_t t0, int64_t len, int64_t Tc, int64_t S, int G, Variant vr) {
-    static_assert(VAR == 0 || NS == 1, "model variants run one thread per channel");
-    constexpr int N = NT * NS;
     constexpr int R = 2 * N * (1 + K);
-    constexpr int DPB = kThreads / NS;
     constexpr bool LR = (VAR & kLowRank) != 0;
     // branch-free tiles (see the step loop); the others keep more state or
     // input conversions in registers and would spill at four waves per SIMD
@@ -1067,8 +1064,7 @@ void k_scan(
     constexpr int KZ = LR ? 1 + K : 0;
 
     const int tid = threadIdx.x;
-    const int ns = tid % NS;
-    const int64_t d_raw = (int64_t)blockIdx.x * DPB + tid / NS;
+    const int64_t d_raw = (int64_t)blockIdx.x * kThreads + tid;
     const bool active = d_raw < D;
     const int64_t d = active ? d_raw : D - 1;
     const int g = blockIdx.y;
@@ -1078,13 +1074,13 @@ void k_scan(
     // A wave without channels ends here: its threads would compute channel D-1
     // from the state that the owner's wave may have replaced already (the
     // sequential evaluation), and store that.
-    const int64_t wave_d = (int64_t)blockIdx.x * DPB + __builtin_amdgcn_readfirstlane(tid / 64) * (64 / NS);
+    const int64_t wave_d = (int64_t)blockIdx.x * kThreads + __builtin_amdgcn_readfirstlane(tid / 64) * 64;
     if (ts >= te || wave_d >= D) return;
 
-    float Af[NT], At[NT], Ai[NT];
+    float Af[N], At[N], Ai[N];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        Af[i] = A[d * N + ns * NT + i];
+    for (int i = 0; i < N; ++i) {
+        Af[i] = A[d * N + i];
         At[i] = Af[i] * kLog2e;
         if constexpr ((VAR & kZoh) != 0) Ai[i] = 1.0f / Af[i];
     }
@@ -1093,19 +1089,18 @@ void k_scan(
     float Dr = 0.0f;
     if constexpr ((VAR & kOutMap) != 0 && OUT) Dr = vr.D_res ? vr.D_res[d] : 0.0f;
 
-    float h[NT], dh[K][NT];
+    float h[N], dh[K][N];
     if constexpr (OUT) {
         const float *ib = init + b * ibs + g * igs + d;
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int n = ns * NT + i;
-            h[i] = ib[n * D];
+        for (int i = 0; i < N; ++i) {
+            h[i] = ib[i * D];
 #pragma unroll
-            for (int k = 0; k < K; ++k) dh[k][i] = ib[(1 + k) * ics + n * D];
+            for (int k = 0; k < K; ++k) dh[k][i] = ib[(1 + k) * ics + i * D];
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
+        for (int i = 0; i < N; ++i) {
             h[i] = 0.0f;
 #pragma unroll
             for (int k = 0; k < K; ++k) dh[k][i] = 0.0f;
@@ -1203,9 +1198,8 @@ void k_scan(
 #pragma unroll
                 for (int k = 0; k < K; ++k) dyv[k] = 0.0f;
 #pragma unroll
-                for (int i = 0; i < NT; ++i) {
-                    const int n = ns * NT + i;
-                    const float Bn = rec[n];
+                for (int i = 0; i < N; ++i) {
+                    const float Bn = rec[i];
                     const float a = transition(delta, At[i]);
                     const float sv = a * h[i];
                     const float gv = Af[i] * sv;
@@ -1220,7 +1214,7 @@ void k_scan(
                         const float r = fmaf(a, Bx, gv);
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
-                            const float dBn = rec[(1 + k) * N + n];
+                            const float dBn = rec[(1 + k) * N + i];
                             const float jk = e * fmaf(dBn, xv, Bn * dxc[k][j]);
                             dh[k][i] = fmaf(a, dh[k][i], fmaf(dD[k], r, jk));
                         }
@@ -1228,25 +1222,22 @@ void k_scan(
                         hn = fmaf(Bn, u, sv);
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
-                            const float dBn = rec[(1 + k) * N + n];
+                            const float dBn = rec[(1 + k) * N + i];
                             dh[k][i] = fmaf(a, dh[k][i], fmaf(gv, dD[k], fmaf(Bn, pk[k], dBn * u)));
                         }
                     }
                     h[i] = hn;
                     if constexpr (OUT) {
-                        const float Cn = rec[(1 + K) * N + n];
+                        const float Cn = rec[(1 + K) * N + i];
                         yv = fmaf(Cn, hn, yv);
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
-                            const float dCn = rec[(2 + K + k) * N + n];
+                            const float dCn = rec[(2 + K + k) * N + i];
                             dyv[k] = fmaf(dCn, hn, fmaf(Cn, dh[k][i], dyv[k]));
                         }
                     }
                 }
                 if constexpr (OUT) {
-                    yv = group_sum<NS>(yv);
-#pragma unroll
-                    for (int k = 0; k < K; ++k) dyv[k] = group_sum<NS>(dyv[k]);
                     if constexpr ((VAR & kOutMap) != 0) {
                         yv = fmaf(Dr, xv, yv);
 #pragma unroll
@@ -1295,27 +1286,23 @@ void k_scan(
         if (end_state) {
             float *eb = end_state + b * ibs + d;
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                const int n = ns * NT + i;
-                eb[n * D] = h[i];
+            for (int i = 0; i < N; ++i) {
+                eb[i * D] = h[i];
 #pragma unroll
-                for (int k = 0; k < K; ++k) eb[(1 + k) * ics + n * D] = dh[k][i];
+                for (int k = 0; k < K; ++k) eb[(1 + k) * ics + i * D] = dh[k][i];
             }
         }
     } else {
         const int64_t base = (b * G + g) * (1 + K);
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int n = ns * NT + i;
-            agg_h[(base * N + n) * D + d] = h[i];
+        for (int i = 0; i < N; ++i) {
+            agg_h[(base * N + i) * D + d] = h[i];
 #pragma unroll
-            for (int k = 0; k < K; ++k) agg_h[((base + 1 + k) * N + n) * D + d] = dh[k][i];
+            for (int k = 0; k < K; ++k) agg_h[((base + 1 + k) * N + i) * D + d] = dh[k][i];
         }
-        if (ns == 0) {
-            agg_s[base * D + d] = sD;
+        agg_s[base * D + d] = sD;
 #pragma unroll
-            for (int k = 0; k < K; ++k) agg_s[(base + 1 + k) * D + d] = sdD[k];
-        }
+        for (int k = 0; k < K; ++k) agg_s[(base + 1 + k) * D + d] = sdD[k];
     }
 }
 
@@ -1848,42 +1835,38 @@ void k_scan_m(
 }
 
 // ---------------------------------------------------------------- k_scan_sh
-// The same scan for NS >= 2 threads per channel.  Per tile of TT steps the
-// block stages in LDS (double-buffered through registers, so the global
+// The same scan with four or eight directions for NS >= 2 threads per channel.
+// Per tile of TT steps the block stages in LDS (double-buffered through registers, so the global
 // loads of tile i+1 overlap the arithmetic of tile i):
 //   s_rec  the TT step records (B, dB_k, C, dC_k), read by every channel;
-//   s_sc   per (t, d): Delta, u = Delta*x, dDelta_k, p_k = dDelta_k*x +
-//          Delta*dx_k, each computed once per channel instead of once per
-//          thread sharing it.  With K >= 4 directions (FOLD) the row is
-//          Delta, u, q = sigma*w*x + Delta (= du/dx), sw = sigma*w and dx_k:
-//          since dDelta_k = sw dx_k and p_k = q dx_k, the tangent's input
-//          terms are dx_k * c with c = sw*g + B*q shared by the directions,
-//          dh_k = (Abar dh_k + dx_k c) + dB_k u: three operations per
-//          direction and lane instead of four, and 4 + K scalars per (t, d)
-//          instead of 2 + 2K.
+//   s_sc   per (t, d): Delta, u = Delta*x, q = sigma*w*x + Delta (= du/dx),
+//          sw = sigma*w and dx_k, each computed once per channel instead of
+//          once per thread sharing it.  Since dDelta_k = sw dx_k and p_k = q
+//          dx_k, the tangent's input terms are dx_k * c with c = sw*g + B*q
+//          shared by the directions, dh_k = (Abar dh_k + dx_k c) + dB_k u:
+//          three operations per direction and lane instead of four, and
+//          4 + K scalars per (t, d) instead of 2 + 2K.
 // Every tile runs all TT steps: the slots of a short last tile hold
-// Delta = u = dDelta_k = p_k = 0, so Abar = 1 and the drive is zero, which
+// Delta = u = q = sw = dx_k = 0, so Abar = 1 and the drive is zero, which
 // leaves h and dh_k exactly unchanged; only their output stores are
 // skipped.  With no early exit the loop keeps the state in place (an exit
 // inside the loop made the compiler copy the state on every step).
-// The output pass with one or two directions, or four in pairs of threads,
-// is held to three waves per SIMD (168 VGPRs; N = 64 at pulse128k sizes
-// 5.16 -> 4.13 ms per pass); wider ones spill there and keep two.
+// The output pass with four directions in pairs of threads is held to three
+// waves per SIMD (168 VGPRs); wider ones spill there and keep two.
 template <int NT, int NS, int K, bool OUT, typename InT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT && (K <= 2 || (K == 4 && NS == 2)) ? 3 : 1))) void k_scan_sh(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT && K == 4 && NS == 2 ? 3 : 1))) void k_scan_sh(
     const InT *__restrict__ x, const InT *__restrict__ dx, const float *__restrict__ A,
     const float *__restrict__ w_delta, const float *__restrict__ b_delta, const float *__restrict__ bc,
     const float *__restrict__ init, int64_t ibs, int64_t igs, int64_t ics,
     float *__restrict__ y, float *__restrict__ dy, float *__restrict__ end_state,
     float *__restrict__ agg_h, float *__restrict__ agg_s,
     int64_t Bsz, int64_t L, int64_t D, int64_t t0, int64_t len, int64_t Tc, int64_t S, int G, Variant) {
-    static_assert(NS >= 2, "one thread per channel uses k_scan");
+    static_assert(NS >= 2 && K >= 4, "one thread per channel uses k_scan, one or two directions k_scan_m");
     constexpr int N = NT * NS;
     constexpr int R = 2 * N * (1 + K);
     constexpr int DPB = kThreads / NS;       // channels per block
     constexpr int TT = 8;                    // steps per tile
-    constexpr bool FOLD = K >= 4;            // the direction-shared form above
-    constexpr int SCW = FOLD ? 4 + K : 2 + 2 * K;   // per-(t, d) scalars
+    constexpr int SCW = 4 + K;               // per-(t, d) scalars
     constexpr int SCP = (SCW + 3) / 4 * 4;   // 16-byte rows: 128-bit reads
     constexpr int RV4 = (TT * R / 4 + kThreads - 1) / kThreads;  // record float4s per thread
     constexpr int TQ = (TT * DPB + kThreads - 1) / kThreads;     // (t, d) tasks per thread
@@ -1999,19 +1982,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
             float *o = &s_sc[tt][j][0];
             o[0] = delta;
             o[1] = delta * xq[i];
-            if constexpr (FOLD) {
-                o[2] = fmaf(sw, xq[i], delta);
-                o[3] = sw;
+            o[2] = fmaf(sw, xq[i], delta);
+            o[3] = sw;
 #pragma unroll
-                for (int k = 0; k < K; ++k) o[4 + k] = live ? dxq[i][k] : 0.0f;
-            } else {
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float ddl = sw * dxq[i][k];
-                    o[2 + k] = ddl;
-                    o[2 + K + k] = fmaf(ddl, xq[i], delta * dxq[i][k]);
-                }
-            }
+            for (int k = 0; k < K; ++k) o[4 + k] = live ? dxq[i][k] : 0.0f;
         }
     };
 
@@ -2027,28 +2001,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
         for (int tt = 0; tt < TT; ++tt) {
             const int64_t t = tb + tt;
             const float *sc = &s_sc[tt][dl][0];
-            const float delta = sc[0], u = sc[1];
-            float dD[K], pk[K];     // FOLD: pk unused, dD holds dx_k
-            float qv = 0.0f, swv = 0.0f;
-            if constexpr (FOLD) {
-                qv = sc[2];
-                swv = sc[3];
+            const float delta = sc[0], u = sc[1], qv = sc[2], swv = sc[3];
+            float dxv[K];
 #pragma unroll
-                for (int k = 0; k < K; ++k) dD[k] = sc[4 + k];
-            } else {
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    dD[k] = sc[2 + k];
-                    pk[k] = sc[2 + K + k];
-                }
-            }
+            for (int k = 0; k < K; ++k) dxv[k] = sc[4 + k];
             if constexpr (!OUT) {
                 sD += delta;
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    if constexpr (FOLD) sdD[k] = fmaf(swv, dD[k], sdD[k]);
-                    else sdD[k] += dD[k];
-                }
+                for (int k = 0; k < K; ++k) sdD[k] = fmaf(swv, dxv[k], sdD[k]);
             }
             const float *rec = s_rec + tt * R;
             float yv = 0.0f, dyv[K];
@@ -2065,28 +2025,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OUT &&
                 const float gv = Af[i] * sv;
                 const float hn = fmaf(Bn, u, sv);
                 // The tangent is accumulated in place, scaled first:
-                // dh = ((a dh + g dDelta) + B p) + dB u.  Ending the chain on
+                // dh = (a dh + dx c) + dB u.  Ending the chain on
                 // dh itself keeps each dh_k in one register across steps (the
                 // form a dh + (...) ends in a temporary, which this loop then
                 // copied back on every step).
-                if constexpr (FOLD) {
-                    const float c = fmaf(swv, gv, Bn * qv);
+                const float c = fmaf(swv, gv, Bn * qv);
 #pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const float dBn = rec[(1 + k) * N + n];
-                        float v = a * dh[k][i];
-                        v = fmaf(dD[k], c, v);
-                        dh[k][i] = fmaf(dBn, u, v);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const float dBn = rec[(1 + k) * N + n];
-                        float v = a * dh[k][i];
-                        v = fmaf(gv, dD[k], v);
-                        v = fmaf(Bn, pk[k], v);
-                        dh[k][i] = fmaf(dBn, u, v);
-                    }
+                for (int k = 0; k < K; ++k) {
+                    const float dBn = rec[(1 + k) * N + n];
+                    float v = a * dh[k][i];
+                    v = fmaf(dxv[k], c, v);
+                    dh[k][i] = fmaf(dBn, u, v);
                 }
                 h[i] = hn;
                 if constexpr (OUT) {
@@ -2172,7 +2121,7 @@ template <int NT, int NS, int K, bool OUT, typename InT, int VAR>
 constexpr auto scan_kernel() {
     constexpr int V = OUT ? VAR : (VAR & (kZoh | kGroups | kLowRank));
     if constexpr (NT == 16) return &k_scan_m<NS, K, OUT, InT, V>;
-    else if constexpr (NS == 1) return &k_scan<NT, NS, K, OUT, InT, V>;
+    else if constexpr (NS == 1) return &k_scan<NT, K, OUT, InT, V>;
     else return &k_scan_sh<NT, NS, K, OUT, InT>;
 }
 

@@ -131,8 +131,7 @@ int main() {
                     pgf::LaPlan lq;
                     if (pgf::make_la_plan(&a, &lq) == PGF_OK) {
                         ++la;
-                        CHECK(lq.state % 256 == 0 && lq.rec % 256 == 0 && lq.agg_h % 256 == 0 &&
-                              lq.agg_s % 256 == 0 && lq.total % 256 == 0);
+                        CHECK(lq.state % 256 == 0 && lq.agg_h % 256 == 0 && lq.agg_s % 256 == 0 && lq.total % 256 == 0);
                         CHECK(lq.n_chunks * lq.chunk_len >= lq.L);
                     }
                 }
