@@ -31,9 +31,10 @@ constexpr int64_t kSimds = 1024;
 // of ten thousand steps still give the GPU several waves per SIMD (it never
 // depends on L).  Shorter segments cost traffic: each adds its state planes
 // four times (written by the aggregate pass, read and written by the carry,
-// read by the output pass).  One direction at B = 1, D = 1536, N = 16 (24
-// waves a column), L = 8192 / 131072, in us: 256 steps 290 / 2190, 128 steps
-// 200 / 2220.  With more than two state planes 256 holds down to 32 waves.
+// read by the output pass).  At B = 1, D = 1536, N = 16 (24 waves a column),
+// L = 8192 / 131072, in us, 256-step segments against 128-step ones: one
+// direction 282 / 2400 and 220 / 2474, the parameter flows 348 / 2171 and
+// 246 / 2304.  With more than two state planes 256 holds down to 32 waves.
 // Not below 32: with few lanes the carry's chain (about 45 ns a segment) takes
 // over on long sequences (16 channels x 131072 steps: 571 us at 256, 722 at 16).
 constexpr int64_t kDefaultSeg = 256;
