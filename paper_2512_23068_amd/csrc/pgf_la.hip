@@ -18,7 +18,7 @@
 // Kernels, per host block of steps [t0, t0+len):
 //   k_la_chunk<false>  zero-start segment aggregates (end states) and the
 //                  segment sums of g and dg_k
-//   k_la_carry     sequential over the block's segments, per lane: a segment
+//   k_la_carry     composes the block's segments, per lane and in order: a segment
 //                  maps (S, dS_k) to (P S + S0, P dS_k + Q_k S + dS0_k) with
 //                  P = exp(sum g), Q_k = P sum dg_k (multiplications only)
 //   k_la_chunk<true>   rescan from the true entry states, writes o and do_k

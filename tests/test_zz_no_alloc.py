@@ -32,7 +32,7 @@ def _assert_equal(ref, got, what):
 
 
 def test_noalloc_two_calls_match_scan_jvp():
-    # first a larger call (1536 channels, 8 host blocks of 2048 steps), then a
+    # first a larger call (1536 channels, 16 host blocks of 1024 steps), then a
     # smaller one with two directions: the second must read nothing of what
     # the first left in the scratch
     big = gu.custom("mamba130m", seqlen=16000, d_inner=1536)
